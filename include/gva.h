@@ -336,6 +336,24 @@ int gva_prefill_attention(const gva_dims* dims, int32_t n_new, const float* q_ab
                           float* lse, void* stream);
 
 /*
+ * gva_prefill_workspace_size, gva_prefill -- gva_prefill_absorb and
+ * gva_prefill_attention in one call: o and lse of a prompt's rows from the
+ * raw queries q [B][n_new][H][d_c+d_r] and the maps m.  Where the grid is
+ * large enough the absorption runs inside the attention launch and the
+ * absorbed queries never reach memory; otherwise (short prompts) the call
+ * makes the two launches, with the absorbed queries in `workspace`, a
+ * caller-owned device buffer of at least the bytes
+ * gva_prefill_workspace_size reports for the same dims and n_new on the
+ * current device, 256-byte aligned (0 bytes: workspace may be NULL).  Its
+ * contents are scratch.  Shapes, checks and outputs as for the two calls;
+ * a workspace that is missing, short or misaligned: GVA_ERR_INVALID_ARG.
+ */
+int gva_prefill_workspace_size(const gva_dims* dims, int32_t n_new, size_t* bytes);
+int gva_prefill(const gva_dims* dims, int32_t n_new, const void* q, const void* m, const void* v_cache,
+                const void* kr_cache, const int32_t* lens, void* workspace, size_t workspace_bytes, float* o,
+                float* lse, void* stream);
+
+/*
  * gva_gqa_prefill_attention -- the matched grouped-query prefill the paper
  * compares GVA against: the same causal rows, scores q[b][i][h] . k_cache
  * [b][g(h)][t] over an explicit key stream of width d_v (no positional

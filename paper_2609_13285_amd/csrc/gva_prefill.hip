@@ -1,7 +1,10 @@
 // libgva.so -- causal prefill of GVA (Algorithm 1 for every prompt position at
-// once): prefill_bf16_kernel (the waves of a workgroup split its key tiles),
-// prefill_vt_kernel (the waves split its columns and share each tile's V^T),
-// gva_prefill_attention and the matched-GQA baseline gva_gqa_prefill_attention.
+// once): prefill_lds_kernel (key tiles shared through LDS, the absorption
+// fused), prefill_bf16_kernel (the waves of a workgroup split its key tiles,
+// for launches of few workgroups), gva_prefill, gva_prefill_attention and the
+// matched-GQA baseline gva_gqa_prefill_attention.
+
+#include <type_traits>
 
 #include "gva_common.h"
 
@@ -52,6 +55,10 @@ struct PrefillParams {
   float* lse;             // [B][N][H]
   int32_t B, H, G, N, d_r, t_max, n_qblocks;
   float scale_log2;
+  const void* q;          // fused absorption: the raw query [B][N][H][d_c + d_r] and the
+  const void* m;          // maps [H][d_v][d_c] (q_abs and q_rot NULL)
+  int32_t d_c;
+  double inv_freq[kMaxPairs];
 };
 
 constexpr float kLazyMax = 8.f;
@@ -395,364 +402,503 @@ __global__ void __launch_bounds__(kThreads, prefill_min_blocks(NRC)) prefill_bf1
   }
 }
 
-// ----------------------------------------------- prefill, columns per wave
-// The same causal prefill with the work divided the other way: each of the
-// four waves owns CW (position, head) columns of its own and walks every
-// key tile of the workgroup's range, so the waves hold disjoint softmax
-// states and write their own outputs (no merge).  All four waves work on
-// one key tile at a time and share its V^T: wave w transposes NB / 4 of
-// the tile's 16-wide value blocks (identity products, fp16) into LDS, and
-// after one barrier every wave reads all NB blocks for its P.V.  Per tile a
-// wave then issues a quarter of the identity products (2 NB / 4 instead of
-// 2 NB) and converts a quarter of the blocks to fp16; the V tile itself is
-// read by all four waves from the cache hierarchy (the same rows at the
-// same time).
-// Columns per wave: 32, or 16 for the matched-GQA baseline, whose separate
-// key tile takes the registers of the second column block.
-__host__ __device__ constexpr int prefill_vt_cols(int dv, bool gqa) { return gqa ? 16 : (dv >= 128 ? 32 : 64); }
+using PrefillFn = void (*)(PrefillParams);
 
-template <int HPG, int DV, int NRC, bool GQA, bool KPACK>
-__global__ void __launch_bounds__(kThreads, 2) prefill_vt_kernel(PrefillParams p) {
-  static_assert(!KPACK || NRC == 1, "a packed positional chunk is a single chunk");
+constexpr int kPrefillCols = 128;             // (position, head) columns per workgroup of prefill_lds_kernel
+
+// ------------------------------------------ prefill, key tiles shared in LDS
+// The prompt kernel.  A workgroup takes 128 (position, head) columns of one
+// group, 32 per wave (a wave's columns: 32 positions of one head, or 16 of
+// each of two at H/G = 8), and its four waves walk the key tiles together;
+// with KS = 2 a second set of four waves takes every other tile of the same
+// columns and the two are merged at the end.
+//
+// Per 32-row tile, on 32x32x16 products (lane = column, registers = rows):
+//  - the tile's value and positional-key rows are copied into LDS by the
+//    waves, a quarter each, two tiles ahead (buffer loads straight to LDS,
+//    three buffers), so no wave holds a tile in registers and each row is
+//    requested once per workgroup;
+//  - every wave reads them as A operands for its scores S^T = [V | kr] q^T,
+//    the query's bf16 high and low parts both in registers as B operands.
+//    The accumulator starts at minus the column's running maximum, so the
+//    products arrive as the softmax's exponents;
+//  - wave w turns value block w (at d_v = 64, waves 0 and 1) into V^T in fp16
+//    with identity products and puts it in LDS for all four (two buffers), in
+//    the row order in which the score registers lie, so a wave's softmax
+//    weights are the B operand of its P.V as they are;
+//  - P.V runs one tile behind the scores, its products between the softmax's
+//    exponentials.
+// One barrier per tile.
+//
+// What bounds it: at d_v = 128 the matrix cores' power.  They are busy 63% of
+// the cycles, at which the clock settles at 1.9 GHz (a large bf16 library
+// product: 70% at 2.0 GHz; the kernel this replaced, every wave reading whole
+// tiles into registers and transposing in 16-wide products: 49% at 2.3 GHz).
+// At d_v = 64 the softmax, twice as much per product.  Measured, whole calls
+// from the raw queries against the separate absorption and the former
+// kernels: H32 G8 d 128/16, 8192 tokens 878 -> 748 us; H16 G4 d 64/16, four
+// 2048-token prompts 131 -> 75 us; the matched-GQA baseline at H32 G8 d 128,
+// 4096 tokens 310 -> 202 us.  Three waves per SIMD at d_v = 64 (168
+// registers) spill and lose (8192 tokens 240 -> 258 us).
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 mfma32(f16x8 a, f16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ i32x4 buffer_desc(const void* p, int bytes) {
+  const uint64_t a = (uint64_t)(uintptr_t)p;
+  return i32x4{(int)(uint32_t)a, (int)((a >> 32) & 0xFFFFu), bytes, kBufferWord3};
+}
+
+// One wave copies 1 KB into LDS, 16 bytes per lane in lane order: bytes
+// [soff, soff + 1024) behind the descriptor (zeros past its end) to LDS
+// address dst.  In asm because the compiler, which cannot tell the tile
+// buffers apart, would otherwise drain every copy in flight before each LDS
+// read; the kernel waits for its own copies (wait_copies) before the barrier
+// that hands a tile over.  The copy writes no register but m0, which the
+// compiler keeps nothing in across statements.
+__device__ __forceinline__ void copy_kb(i32x4 desc, uint32_t dst, int voff, int soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               ::"s"(dst), "v"(voff), "s"(desc), "s"(soff)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_copies() {   // until at most N of this wave's copies are in flight
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// row of a 32-row tile in score register r of a lane in half h
+__device__ __forceinline__ constexpr int score_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
+
+template <int DV, int NRC, bool GQA, int KS>
+struct PrefillCfg {
+  static constexpr int NCH = DV / 16;                      // 16-wide K-chunks of a value row
+  static constexpr int NIB = DV / 32;                      // 32-wide output blocks
+  static constexpr int V_BYTES = kTileRows * DV * 2;
+  static constexpr int KB = V_BYTES / 1024;                // KB per value tile
+  static constexpr int TILE_BYTES = V_BYTES * (GQA ? 2 : 1) + NRC * 1024;
+  static constexpr int VT_BYTES = V_BYTES;
+  static constexpr int GROUP_BYTES = 3 * TILE_BYTES + 2 * VT_BYTES;   // one set of four waves
+  // operands read from LDS ahead of their products: scores, and of the P.V's
+  // V^T before the softmax (fewer where four positional chunks hold the registers)
+  static constexpr int READ_AHEAD = DV >= 128 && NRC > 2 ? 3 : 5;
+  static constexpr int VT_AHEAD = DV >= 128 && NRC > 2 ? 1 : 4;
+  static constexpr int COPIES = KB / 4 * (GQA ? 2 : 1) + (NRC > 0 ? 1 : 0);   // per wave and tile
+  static constexpr int MERGE_BYTES = KS > 1 ? kWaves * 64 * (NIB * 16 + 2) * 4 : 0;
+  static constexpr int LDS = KS * GROUP_BYTES > MERGE_BYTES ? KS * GROUP_BYTES : MERGE_BYTES;
+};
+
+template <int DV, int NRC, bool GQA, int KS>
+__global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams p) {
+  using Cfg = PrefillCfg<DV, NRC, GQA, KS>;
   static_assert(!GQA || NRC == 0, "the GQA baseline has no positional term");
-  constexpr int CW = prefill_vt_cols(DV, GQA), NC = DV / 32, NB = DV / 16, CB = CW / 16;
-  constexpr int WCOLS = kWaves * CW;           // columns per workgroup
-  constexpr int QB = WCOLS / HPG;              // positions per workgroup
-  constexpr int KPW = NB / kWaves;             // V^T blocks each wave transposes
-  static_assert(KPW >= 1 && NB % kWaves == 0, "every wave transposes whole blocks");
-  constexpr int DEPTH = 2;
-  constexpr int NLO = NC + (KPACK ? 0 : NRC);
-  // P.V one tile behind the scores (below), except in the matched-GQA
-  // baseline, which ran slower so; kAhead column blocks' scores are issued
-  // before that P.V: one where a separate positional chunk and its low parts
-  // already hold the registers (all of them would spill), else all
-  constexpr bool kPipe = !GQA;
-  constexpr int kAhead = (NRC > 0 && !KPACK) ? 1 : CB;
-  __shared__ bf16x8 lo_lds[kWaves * CB * NLO * 64];   // the low query parts, per wave
-  __shared__ f16x8 vt_lds[2 * NB * 64];               // V^T blocks of a tile, two buffers
+  constexpr int NCH = Cfg::NCH, NIB = Cfg::NIB, RA = Cfg::READ_AHEAD, VA = Cfg::VT_AHEAD;
+  __shared__ __attribute__((aligned(1024))) char lds[Cfg::LDS];
 
+  const int hpg = p.H / p.G;
   const int nbg = p.B * p.G;
   const int x = blockIdx.x;
   const int qb = p.n_qblocks - 1 - x / nbg;    // longest query blocks first
   const int b = (x % nbg) / p.G, g = (x % nbg) % p.G;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = lane & 15, qd = lane >> 4;
-  const int h0 = g * HPG;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = KS > 1 ? wave >> 2 : 0, w = wave & 3;
+  const int n = lane & 31, h = lane >> 5;      // column, and half of the rows / K-chunk
   const bf16x8 zero8 = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
 
+  // ---- this wave's columns: position i (of the prompt), head
+  const int ppb = kPrefillCols / hpg;          // positions per workgroup
+  const int wpos = qb * ppb + (hpg < 4 ? (w / hpg) * 32 : 0);   // the wave's first position
+  const int head = g * hpg + (hpg < 4 ? w % hpg : (hpg == 4 ? w : 2 * w + (n >> 4)));
+  const int i_col = wpos + (hpg == 8 ? n & 15 : n);
   const int L = clamp_len(p.lens, b, p.t_max);
-  const int i_end = min(p.N, (qb + 1) * QB);
-  const int kend = L - p.N + i_end;            // rows the block's last position sees
-  // column CW w + 16 cb + n of this lane: position i = qb QB + col / HPG,
-  // head h0 + col % HPG; pos[cb] = its position, or -1 if it has none
-  int pos[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    const int col = CW * w + 16 * cb + n;
-    const int i = qb * QB + col / HPG;
-    const int ps = L - p.N + i;
-    pos[cb] = (i < p.N && ps >= 0) ? ps : -1;
-  }
-  const int p_first = L - p.N + qb * QB + (CW * w) / HPG;   // this wave's first position
+  const int kend = L - p.N + min(p.N, (qb + 1) * ppb);          // rows the block's last position sees
+  const int p_first = L - p.N + wpos;
+  const int pos = (i_col < p.N && L - p.N + i_col >= 0) ? L - p.N + i_col : -1;
+  const int64_t qrow = ((int64_t)b * p.N + min(i_col, p.N - 1)) * p.H + head;
 
-  // ---- key tiles: rows [0, kend), every wave all of them
-  const int kend16 = kend > 0 ? ((kend + kLayoutRows - 1) / kLayoutRows) * kLayoutRows : 0;
-  const uint16_t* vbase = static_cast<const uint16_t*>(p.v) + ((int64_t)b * p.G + g) * p.t_max * DV;
-  const uint16_t* kbase = static_cast<const uint16_t*>(p.kr) + (int64_t)b * p.t_max * p.d_r;
-  const __amdgpu_buffer_rsrc_t vres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(vbase), (short)0, kend16 * DV * 2, kBufferWord3);
-  const __amdgpu_buffer_rsrc_t kres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(kbase), (short)0, NRC > 0 ? kend16 * p.d_r * 2 : 0, kBufferWord3);
-  const __amdgpu_buffer_rsrc_t kcres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(GQA ? static_cast<const void*>(static_cast<const uint16_t*>(p.k_gqa) +
-                                                       ((int64_t)b * p.G + g) * p.t_max * DV)
-                            : static_cast<const void*>(vbase)),
-      (short)0, kend16 * DV * 2, kBufferWord3);
-  const int kpieces = p.d_r / 8;
-  const int v_lane = qd * 256 + n * 16;
-  int k_lane[NRC > 0 ? NRC : 1];
-#pragma unroll
-  for (int rc = 0; rc < NRC; ++rc) {
-    const int piece = KPACK ? (qd < 2 * kpieces ? qd % kpieces : 0) : min(4 * rc + qd, kpieces - 1);
-    k_lane[rc] = piece * 256 + n * 16;
-  }
-  const int v_tile_bytes = 16 * DV * 2, k_tile_bytes = 16 * p.d_r * 2;
+  // ---- tile copies.  The descriptors end at the last layout tile.
+  const int kend16 = kend > 0 ? (kend + kLayoutRows - 1) / kLayoutRows * kLayoutRows : 0;
+  const int64_t vstream = ((int64_t)b * p.G + g) * p.t_max * DV;
+  const i32x4 vdesc = buffer_desc(static_cast<const uint16_t*>(p.v) + vstream, kend16 * DV * 2);
+  const i32x4 kcdesc = buffer_desc(GQA ? static_cast<const uint16_t*>(p.k_gqa) + vstream : nullptr, kend16 * DV * 2);
+  const i32x4 kdesc = buffer_desc(static_cast<const uint16_t*>(p.kr) + (int64_t)b * p.t_max * p.d_r,
+                                  NRC > 0 ? kend16 * p.d_r * 2 : 0);
+  char* const grp_lds = lds + grp * Cfg::GROUP_BYTES;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)grp_lds;
   const int ntiles = kend > 0 ? (kend + kTileRows - 1) / kTileRows : 0;
-  using TileT = Tile<DV, NRC, GQA>;
-  auto load_tile = [&](TileT& t, int row0) {
-    const int lt = row0 / kLayoutRows;
+  const int nit = (ntiles + KS - 1) / KS;      // the same for both sets of waves (they share the barriers)
+  auto tile_row = [&](int j) { return (KS * j + grp) * kTileRows; };
+  auto copy_tile = [&](int row0, int buf) {
+    const uint32_t dst = lds0 + buf * Cfg::TILE_BYTES;
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-      const int vsoff = (lt + hf) * v_tile_bytes;
-      if constexpr (GQA) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-          t.kc[hf][c] = as_bf16x8(__builtin_amdgcn_raw_buffer_load_b128(kcres, v_lane + 1024 * c, vsoff, 0));
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-        t.v[hf][c] = as_bf16x8(__builtin_amdgcn_raw_buffer_load_b128(vres, v_lane + 1024 * c, vsoff, 0));
-#pragma unroll
-      for (int rc = 0; rc < NRC; ++rc)
-        t.k[hf][rc] = as_bf16x8(__builtin_amdgcn_raw_buffer_load_b128(kres, k_lane[rc], (lt + hf) * k_tile_bytes, 0));
+    for (int k = 0; k < Cfg::KB / 4; ++k) {
+      const int kb = w * (Cfg::KB / 4) + k;
+      copy_kb(vdesc, dst + kb * 1024, lane * 16, row0 * DV * 2 + kb * 1024);
+      if constexpr (GQA) copy_kb(kcdesc, dst + Cfg::V_BYTES + kb * 1024, lane * 16, row0 * DV * 2 + kb * 1024);
+    }
+    // the positional tile is 32 d_r 2 bytes <= NRC KB: copied in whole KBs
+    // (what follows it lands in padding), by as many waves as it takes, the
+    // others repeating one of them so that every wave makes as many copies
+    if constexpr (NRC > 0) {
+      const int kb = w % NRC;
+      copy_kb(kdesc, dst + Cfg::V_BYTES + kb * 1024, lane * 16, row0 * p.d_r * 2 + kb * 1024);
     }
   };
-  TileT buf[DEPTH];
-  load_tile(buf[0], 0);
-  load_tile(buf[1], kTileRows);
-  __builtin_amdgcn_sched_barrier(0);
+  copy_tile(tile_row(0), 0);
+  copy_tile(tile_row(1), 1);
 
-  // ---- this wave's queries as bf16 high + low B operands (zero for columns
-  // with no position); the low parts to this wave's LDS region
-  bf16x8 bq[CB][NC];
-  bf16x8 bk[CB][NRC > 0 ? NRC : 1];
-  bf16x8* my_lo = lo_lds + w * (CB * NLO * 64);
+  // ---- the queries as bf16 high and low B operands: lane (n, h) holds
+  // entries 16 c + 8 h .. + 7 of its column's query
+  bf16x8 qh[NCH], ql[NCH], rh[NRC > 0 ? NRC : 1], rl[NRC > 0 ? NRC : 1];
+  auto put_query = [&](bf16x8& hi, bf16x8& lo, float* xv) {
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    const int col = CW * w + 16 * cb + n;
-    const int i = min(qb * QB + col / HPG, p.N - 1);
-    const int64_t qrow = ((int64_t)b * p.N + i) * p.H + h0 + col % HPG;
-    const float* qa = p.q_abs + qrow * DV + 8 * qd;
+    for (int j = 0; j < 8; ++j) xv[j] *= p.scale_log2;
+    hi = pos >= 0 ? split_hi_lo(xv, false) : zero8;
+    lo = pos >= 0 ? split_hi_lo(xv, true) : zero8;
+  };
+  if (!GQA && p.q != nullptr) {
+    // Fused absorption: q~^T[i][col] = sum_k M_h[i][k] q[col][k] on the same
+    // products.  Row m of an A operand is row i(m) of M_h, bits 2 and 3 of m
+    // swapped, so that a lane's 16 results of a block are two B operands of
+    // the score product as they lie.  At H/G = 8 a wave holds two heads, each
+    // with half of the columns: one pass per head, each keeping its own columns.
+    const int W = p.d_c + p.d_r;
+    const uint16_t* qraw = static_cast<const uint16_t*>(p.q) + qrow * W;
+    f32x16 d[NIB];
+    const int mrow = (n & 19) | ((n & 4) << 1) | ((n & 8) >> 1);
+    const int npass = hpg == 8 ? 2 : 1;
+    constexpr int CS = 4;                      // 16-column chunks per load round
+    const int nround = (p.d_c + 16 * CS - 1) / (16 * CS);
+    for (int ps = 0; ps < npass; ++ps) {
+      const bool mine = npass == 1 || (n >> 4) == ps;
+      const int hd = npass == 1 ? g * hpg + (hpg < 4 ? w % hpg : w) : g * hpg + 2 * w + ps;
+      const uint16_t* mh = static_cast<const uint16_t*>(p.m) + ((int64_t)hd * DV + mrow) * p.d_c;
+      f32x16 e[NIB];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const f32x4 u0 = *reinterpret_cast<const f32x4*>(qa + 32 * c);
-      const f32x4 u1 = *reinterpret_cast<const f32x4*>(qa + 32 * c + 4);
+      for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) e[ib][r] = 0.f;
+      for (int ro = 0; ro < nround; ++ro) {
+        u32x4 xq[CS], xm[CS][NIB];
+#pragma unroll
+        for (int c = 0; c < CS; ++c) {         // columns past d_c: any valid ones against zeros
+          const int col = min(16 * (CS * ro + c) + 8 * h, p.d_c - 8);
+          xq[c] = *reinterpret_cast<const u32x4*>(qraw + col);
+#pragma unroll
+          for (int ib = 0; ib < NIB; ++ib)
+            xm[c][ib] = *reinterpret_cast<const u32x4*>(mh + (int64_t)(32 * ib) * p.d_c + col);
+        }
+#pragma unroll
+        for (int c = 0; c < CS; ++c) {
+          const bf16x8 bq = 16 * (CS * ro + c) < p.d_c ? as_bf16x8(xq[c]) : zero8;
+#pragma unroll
+          for (int ib = 0; ib < NIB; ++ib) e[ib] = mfma32(as_bf16x8(xm[c][ib]), bq, e[ib]);
+        }
+      }
+#pragma unroll
+      for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) d[ib][r] = ps == 0 || mine ? e[ib][r] : d[ib][r];
+    }
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
       float xv[8];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        xv[j] = u0[j] * p.scale_log2;
-        xv[4 + j] = u1[j] * p.scale_log2;
-      }
-      bq[cb][c] = pos[cb] >= 0 ? split_hi_lo(xv, false) : zero8;
-      my_lo[(cb * NLO + c) * 64 + lane] = pos[cb] >= 0 ? split_hi_lo(xv, true) : zero8;
+      for (int j = 0; j < 8; ++j) xv[j] = d[c >> 1][8 * (c & 1) + j];
+      put_query(qh[c], ql[c], xv);
     }
 #pragma unroll
     for (int rc = 0; rc < NRC; ++rc) {
-      const bool hi_slot = KPACK ? qd < kpieces : 32 * rc + 8 * qd < p.d_r;
-      const bool lo_slot = KPACK && qd >= kpieces && qd < 2 * kpieces;
-      const int j0 = KPACK ? 8 * (lo_slot ? qd - kpieces : qd) : 32 * rc + 8 * qd;
+      const int piece = 2 * rc + h;
       float xv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if (hi_slot || lo_slot) {
-        const float* qr = p.q_rot + qrow * p.d_r + j0;
+      if (8 * piece < p.d_r) {
+        const u32x4 raw = *reinterpret_cast<const u32x4*>(qraw + p.d_c + 8 * piece);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          rotate_query_pair(bf16_bits_to_f32(raw[k] & 0xFFFFu), bf16_bits_to_f32(raw[k] >> 16),
+                            (double)(pos > 0 ? pos : 0) * p.inv_freq[4 * piece + k], 1.f, xv[2 * k], xv[2 * k + 1]);
+      }
+      put_query(rh[rc], rl[rc], xv);
+    }
+  } else {
+    const float* qa = p.q_abs + qrow * DV + 8 * h;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      const f32x4 u0 = *reinterpret_cast<const f32x4*>(qa + 16 * c);
+      const f32x4 u1 = *reinterpret_cast<const f32x4*>(qa + 16 * c + 4);
+      float xv[8] = {u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]};
+      put_query(qh[c], ql[c], xv);
+    }
+#pragma unroll
+    for (int rc = 0; rc < NRC; ++rc) {
+      const int piece = 2 * rc + h;
+      float xv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      if (8 * piece < p.d_r) {
+        const float* qr = p.q_rot + qrow * p.d_r + 8 * piece;
         const f32x4 u0 = *reinterpret_cast<const f32x4*>(qr);
         const f32x4 u1 = *reinterpret_cast<const f32x4*>(qr + 4);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          xv[j] = u0[j] * p.scale_log2;
-          xv[4 + j] = u1[j] * p.scale_log2;
+          xv[j] = u0[j];
+          xv[4 + j] = u1[j];
         }
       }
-      bk[cb][rc] = (pos[cb] >= 0 && (hi_slot || lo_slot)) ? split_hi_lo(xv, lo_slot) : zero8;
-      if constexpr (!KPACK)
-        my_lo[(cb * NLO + NC + rc) * 64 + lane] = (pos[cb] >= 0 && hi_slot) ? split_hi_lo(xv, true) : zero8;
+      put_query(rh[rc], rl[rc], xv);
     }
   }
-
+  int k_off[NRC > 0 ? NRC : 1];                // LDS offset of this lane's positional piece
+#pragma unroll
+  for (int rc = 0; rc < NRC; ++rc) {           // pieces past d_r: any valid one against a zero query
+    const int piece = 8 * (2 * rc + h) < p.d_r ? 2 * rc + h : 0;
+    k_off[rc] = (n >> 4) * 32 * p.d_r + piece * 256 + (n & 15) * 16;
+  }
+  // identity selectors: E_c[k][n] = (n == k + 16 c)
   bf16x8 esel[2];
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
+  for (int c = 0; c < 2; ++c) {
     u32x4 u = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      if (8 * qd + j == n + 16 * half) u[j >> 1] |= 0x3F80u << (16 * (j & 1));
-    esel[half] = as_bf16x8(u);
+      if (8 * h + j + 16 * c == n) u[j >> 1] |= 0x3F80u << (16 * (j & 1));
+    esel[c] = as_bf16x8(u);
   }
 
-  float m_run[CB], l_run[CB];
-  f32x4 acc[CB][NB];
+  f32x16 acc[NIB], negm;
+  float m_run = 0.f, l_run = 0.f;
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    m_run[cb] = -INFINITY;
-    l_run[cb] = 0.f;
+  for (int r = 0; r < 16; ++r) negm[r] = 0.f;
 #pragma unroll
-    for (int ib = 0; ib < NB; ++ib) acc[cb][ib] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int ib = 0; ib < NIB; ++ib) acc[ib] = negm;
+  f16x8 bp[2];
 
-  f16x8 bp_prev[CB];                           // the previous tile's weights (pipelined P.V)
-  // next_row: the tile requested into t's registers once its scores are issued
-  auto compute_tile = [&](TileT& t, int row0, int vbuf, bool has_prev, int next_row) {
-    if (row0 + kTileRows > kend) {             // rows past the block's keys: zero
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        const bool dead = row0 + 16 * hf + n >= kend;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) t.v[hf][c] = dead ? zero8 : t.v[hf][c];
-        if constexpr (GQA) {
-#pragma unroll
-          for (int c = 0; c < NC; ++c) t.kc[hf][c] = dead ? zero8 : t.kc[hf][c];
-        }
-#pragma unroll
-        for (int rc = 0; rc < NRC; ++rc) t.k[hf][rc] = dead ? zero8 : t.k[hf][rc];
-      }
-    }
-    // this wave's share of the tile's V^T, into LDS first: the other waves
-    // read it after the barrier below
-    f16x8* vt = vt_lds + vbuf * (NB * 64);
-#pragma unroll
-    for (int kk = 0; kk < KPW; ++kk) {
-      const int k = w * KPW + kk;              // 16-wide value block k: chunk k / 2, half k % 2
-      const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      f32x4 t0 = z, t1 = z;
-      const bf16x8 e = (k & 1) ? esel[1] : esel[0];
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-        if (c == (k >> 1)) {
-          t0 = mfma16(t.v[0][c], e, z);
-          t1 = mfma16(t.v[1][c], e, z);
-        }
-      const float tv[8] = {t0[0], t0[1], t0[2], t0[3], t1[0], t1[1], t1[2], t1[3]};
-      vt[k * 64 + lane] = to_f16x8(tv);       // bf16 values: exact in fp16 at these magnitudes
-    }
-    const bool masked = row0 + kTileRows - 1 > p_first;   // some column may not see every row
-    int lo_off = lane;
-    asm volatile("" : "+v"(lo_off));
-    auto scores = [&](int cb, f32x4 (&sc)[2]) {
-      bf16x8 lo[NLO];
-#pragma unroll
-      for (int c = 0; c < NLO; ++c) lo[c] = my_lo[(cb * NLO + c) * 64 + lo_off];
-#pragma unroll
-      for (int hf = 0; hf < 2; ++hf) {
-        sc[hf] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          sc[hf] = mfma16(GQA ? t.kc[hf][c] : t.v[hf][c], bq[cb][c], sc[hf]);
-          sc[hf] = mfma16(GQA ? t.kc[hf][c] : t.v[hf][c], lo[c], sc[hf]);
-        }
-#pragma unroll
-        for (int rc = 0; rc < NRC; ++rc) {
-          sc[hf] = mfma16(t.k[hf][rc], bk[cb][rc], sc[hf]);
-          if constexpr (!KPACK) sc[hf] = mfma16(t.k[hf][rc], lo[NC + rc], sc[hf]);
-        }
-      }
-    };
-    auto softmax = [&](int cb, const f32x4 (&sc)[2]) {
-      float xv[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) xv[k] = sc[k >> 2][k & 3];
-      if (masked) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-          if (row0 + 16 * (k >> 2) + 4 * qd + (k & 3) > pos[cb]) xv[k] = -INFINITY;
-      }
-      float mt = xv[0];
-#pragma unroll
-      for (int k = 1; k < 8; ++k) mt = fmaxf(mt, xv[k]);
-      mt = max_over_rows(mt);
-      const float m_new = fmaxf(m_run[cb], mt);
-      if (__ballot(mt > m_run[cb] + kLazyMax) != 0) {
-        const float alpha = m_new > m_run[cb] ? __builtin_amdgcn_exp2f(m_run[cb] - m_new) : 1.f;
-        l_run[cb] *= alpha;
-#pragma unroll
-        for (int ib = 0; ib < NB; ++ib) acc[cb][ib] *= alpha;
-        m_run[cb] = m_new;
-      }
-      const float m_use = m_run[cb] == -INFINITY ? 0.f : m_run[cb];
-      float pr[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        pr[k] = __builtin_amdgcn_exp2f(xv[k] - m_use);
-        l_run[cb] += pr[k];
-      }
-      return to_f16x8(pr);
-    };
-    if constexpr (kPipe) {
-      // P.V of the previous tile (its V^T in the other buffer, complete since
-      // the previous barrier) is issued with this tile's softmax, so the
-      // matrix cores run it while the vector units work; it comes first in
-      // program order, before any rescale of the accumulators
-      f32x4 sc[CB][2];
-#pragma unroll
-      for (int cb = 0; cb < kAhead; ++cb) scores(cb, sc[cb]);
-      if constexpr (kAhead == CB) load_tile(t, next_row);
-      __builtin_amdgcn_sched_barrier(0);
-      if (has_prev) {
-        const f16x8* vtp = vt_lds + (vbuf ^ 1) * (NB * 64);
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-          const f16x8 av = vtp[k * 64 + lane];
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb) acc[cb][k] = mfma16(av, bp_prev[cb], acc[cb][k]);
-        }
-      }
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) {
-        if (cb >= kAhead) {
-          __builtin_amdgcn_sched_barrier(0);
-          scores(cb, sc[cb]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        bp_prev[cb] = softmax(cb, sc[cb]);
-      }
-      if constexpr (kAhead < CB) load_tile(t, next_row);
-      __syncthreads();                         // every wave's V^T blocks of this tile are in LDS
-    } else {
-      f16x8 bp[CB];
-      f32x4 sc[2][2];
-      scores(0, sc[0]);
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) {
-        if (cb + 1 < CB) scores(cb + 1, sc[(cb + 1) & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-        bp[cb] = softmax(cb, sc[cb & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      load_tile(t, next_row);
-      __syncthreads();                         // every wave's V^T blocks of this tile are in LDS
-#pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        const f16x8 av = vt[k * 64 + lane];
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) acc[cb][k] = mfma16(av, bp[cb], acc[cb][k]);
-      }
-    }
+  const int v_off = (n >> 4) * (DV * 32) + h * 256 + (n & 15) * 16;   // this lane's piece of chunk 0
+  const char* const vt_lane = grp_lds + 3 * Cfg::TILE_BYTES + lane * 16;
+  auto vt_piece = [&](int vbuf, int k) {       // A operand k = 2 ib + c of a tile's V^T
+    return *reinterpret_cast<const f16x8*>(vt_lane + vbuf * Cfg::VT_BYTES + k * 1024);
   };
 
-  // Every wave runs every tile (the barrier inside compute_tile is reached
-  // the same number of times by all four); tile j + 2 is requested into
-  // tile j's registers as soon as tile j's scores no longer need them.
-  // (requests past the block's rows read zeros through the descriptors and
-  // cost no traffic, so they are unconditional and the waits exact)
-  for (int jt = 0; jt < ntiles; jt += DEPTH) {
+  // One tile; FIRST: the workgroup's first, which has no P.V before it and
+  // sets the running maxima.
+  auto step = [&](auto first_tag, int j, int buf) {
+    constexpr bool FIRST = decltype(first_tag)::value;
+    const int row0 = tile_row(j);
+    copy_tile(tile_row(j + 2), buf == 0 ? 2 : buf - 1);
+    const char* vtile = grp_lds + buf * Cfg::TILE_BYTES;
+    const char* ktile = vtile + Cfg::V_BYTES;
+    __builtin_amdgcn_s_setprio(0);
+    // scores, as exponents relative to the running maximum
+    f32x16 s = negm;
+    bf16x8 a[NCH], ar[NRC > 0 ? NRC : 1];
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      const int j = jt + d;
-      if (j >= ntiles) break;
-      compute_tile(buf[d], j * kTileRows, d, j > 0, (j + DEPTH) * kTileRows);
+    for (int c = 0; c < NCH; ++c) a[c] = *reinterpret_cast<const bf16x8*>((GQA ? ktile : vtile) + v_off + c * 512);
+#pragma unroll
+    for (int rc = 0; rc < NRC; ++rc) ar[rc] = *reinterpret_cast<const bf16x8*>(ktile + k_off[rc]);
+    const int tw = w < NIB ? w : 0;
+    bf16x8 at[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) at[c] = *reinterpret_cast<const bf16x8*>(vtile + v_off + (2 * tw + c) * 512);
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      s = mfma32(a[c], qh[c], s);
+      s = mfma32(a[c], ql[c], s);
     }
-  }
-  if (kPipe && ntiles > 0) {                   // P.V of the last tile
-    const f16x8* vtl = vt_lds + ((ntiles - 1) & 1) * (NB * 64);
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      const f16x8 av = vtl[k * 64 + lane];
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) acc[cb][k] = mfma16(av, bp_prev[cb], acc[cb][k]);
+    for (int rc = 0; rc < NRC; ++rc) {
+      s = mfma32(ar[rc], rh[rc], s);
+      s = mfma32(ar[rc], rl[rc], s);
     }
+    // this wave's block of V^T (at d_v = 64 waves 2 and 3 repeat block 0 and drop it)
+    f32x16 t;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t[r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) t = mfma32(at[c], esel[c], t);
+    // the previous tile's V^T
+    f16x8 av[2 * NIB];
+    if constexpr (!FIRST) {
+#pragma unroll
+      for (int k = 0; k < VA; ++k) av[k] = vt_piece((j & 1) ^ 1, k);
+    }
+    // LDS reads run RA operands ahead of the products that use them
+    __builtin_amdgcn_sched_group_barrier(0x100, RA, 0);
+#pragma unroll
+    for (int k = 0; k < NCH + NRC + 2 - RA; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < VA; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 64, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);             // the softmax goes before the other waves' products
+    if (row0 + kTileRows - 1 > p_first) {      // some column may not see every row
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (row0 + score_row(r, h) > pos) s[r] = -INFINITY;
+    }
+    // rows past the block's keys may hold anything (a wave whose columns all
+    // lie past the prompt's last row masks nothing, but its V^T block counts)
+    if (row0 + kTileRows > kend) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (row0 + score_row(r, h) >= kend) t[r] = 0.f;
+    }
+    float mt = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s[r]);
+    {
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
+      mt = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    }
+    // The maximum is the first tile's, and moves when a column's tile
+    // maximum exceeds it by more than kLazyMax (log2 units).  The
+    // accumulators are rescaled after the P.V below, whose weights are
+    // relative to the old maximum.
+    const bool grow = FIRST || __ballot(mt > kLazyMax) != 0;
+    float alpha = 1.f;
+    if (grow) {
+      float m_new = m_run + (FIRST ? mt : fmaxf(mt, 0.f));
+      if (mt == -INFINITY) m_new = m_run;      // no row of the tile is the column's
+      const float d = m_new - m_run;
+      alpha = __builtin_amdgcn_exp2f(-d);
+      m_run = m_new;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[r] -= d;
+        negm[r] = -m_new;
+      }
+      if constexpr (!FIRST) l_run *= alpha;
+    }
+    float pr[16];
+    f16x8 bn[2], tv[2];
+    // P.V of the previous tile with this tile's exponentials between its
+    // products, in the order written (scheduling barriers)
+#pragma unroll
+    for (int k = 0; k < 2 * NIB; ++k) {
+      if constexpr (!FIRST) {
+        acc[k >> 1] = mfma32(av[k], bp[k & 1], acc[k >> 1]);
+        if (k + VA < 2 * NIB) av[k + VA] = vt_piece((j & 1) ^ 1, k + VA);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int r = k * (8 / NIB); r < (k + 1) * (8 / NIB); ++r) {
+        pr[r] = __builtin_amdgcn_exp2f(s[r]);
+        l_run += pr[r];
+      }
+      if (k + 1 == NIB || k + 1 == 2 * NIB) bn[k / NIB] = to_f16x8(pr + 8 * (k / NIB));
+      if (k == 0 || k == NIB) {
+        float x8[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x8[e] = t[8 * (k / NIB) + e];
+        tv[k / NIB] = to_f16x8(x8);            // bf16 values: exact in fp16 at these magnitudes
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    asm volatile("" ::"v"(bn[0]), "v"(bn[1]), "v"(l_run));   // formed here, beside the products, not after them
+    __builtin_amdgcn_sched_barrier(0);
+    if (w < NIB) {
+      char* vt = grp_lds + 3 * Cfg::TILE_BYTES + (j & 1) * Cfg::VT_BYTES + lane * 16;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) *reinterpret_cast<f16x8*>(vt + (2 * w + c) * 1024) = tv[c];
+    }
+    if (!FIRST && grow) {
+#pragma unroll
+      for (int ib = 0; ib < NIB; ++ib) acc[ib] *= alpha;
+    }
+    bp[0] = bn[0];
+    bp[1] = bn[1];
+    wait_copies<Cfg::COPIES>();                // the next tile has landed (the one after it may be in flight)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's V^T block is in LDS
+    __builtin_amdgcn_s_barrier();
+  };
+
+  wait_copies<Cfg::COPIES>();
+  __builtin_amdgcn_s_barrier();
+  if (nit > 0) {
+    step(std::true_type{}, 0, 0);
+    int buf = 1;
+    for (int j = 1; j < nit; ++j) {
+      step(std::false_type{}, j, buf);
+      buf = buf == 2 ? 0 : buf + 1;
+    }
+#pragma unroll
+    for (int k = 0; k < 2 * NIB; ++k) acc[k >> 1] = mfma32(vt_piece((nit - 1) & 1, k), bp[k & 1], acc[k >> 1]);
   }
 
-  // ---- this wave's columns: normalise and write
+  // ---- merge the two sets of waves, normalise, write
+  {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+    l_run = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+  if constexpr (KS > 1) {
+    float* rec = reinterpret_cast<float*>(lds) + w * 64 * (NIB * 16 + 2) + lane;
+    wait_copies<0>();                          // copies past the end still write LDS
+    __syncthreads();
+    if (grp == 1) {
+      rec[0] = m_run;
+      rec[64] = l_run;
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) {
-    const float l = sum_over_rows(l_run[cb]);
-    const int col = CW * w + 16 * cb + n;
-    const int qi = qb * QB + col / HPG;
-    if (qi >= p.N) continue;
-    const bool seen = m_run[cb] != -INFINITY && L - p.N + qi >= 0;
-    const float inv = seen ? 1.f / l : 0.f;
-    const int64_t orow = ((int64_t)b * p.N + qi) * p.H + h0 + col % HPG;
+      for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
-    for (int ib = 0; ib < NB; ++ib) {
-      f32x4 o = acc[cb][ib] * inv;
+        for (int r = 0; r < 16; ++r) rec[64 * (2 + 16 * ib + r)] = acc[ib][r];
+    }
+    __syncthreads();
+    if (grp == 1) return;
+    const float m1 = rec[0], l1 = rec[64];
+    const bool has0 = !(l_run == 0.f), has1 = !(l1 == 0.f);
+    const float mx = has0 && has1 ? fmaxf(m_run, m1) : (has0 ? m_run : m1);
+    const float a0 = has0 ? __builtin_amdgcn_exp2f(m_run - mx) : 0.f;
+    const float a1 = has1 ? __builtin_amdgcn_exp2f(m1 - mx) : 0.f;
+    l_run = l_run * a0 + l1 * a1;
+    m_run = mx;
+#pragma unroll
+    for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[ib][r] = acc[ib][r] * a0 + rec[64 * (2 + 16 * ib + r)] * a1;
+  } else {
+    wait_copies<0>();
+  }
+  if (i_col >= p.N) return;
+  const bool seen = pos >= 0 && !(l_run == 0.f);
+  const float inv = seen ? 1.f / l_run : 0.f;
+#pragma unroll
+  for (int ib = 0; ib < NIB; ++ib)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      f32x4 o;
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) o[jj] = acc[ib][4 * r4 + jj] * inv;
+      if (!seen) o = f32x4{0.f, 0.f, 0.f, 0.f};
       // written once and not read again here: kept out of the L2, which holds
       // the group's key and value rows
-      __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(p.o + orow * DV + 16 * ib + 4 * qd));
+      __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(p.o + qrow * DV + 32 * ib + 8 * r4 + 4 * h));
     }
-    if (qd == 0) p.lse[orow] = seen ? (m_run[cb] + log2f(l)) * kLn2 : -INFINITY;
-  }
+  if (h == 0) p.lse[qrow] = seen ? (m_run + log2f(l_run)) * kLn2 : -INFINITY;
 }
 
-using PrefillFn = void (*)(PrefillParams);
+template <int DV, int KS>
+PrefillFn pick_prefill_lds_nrc(int d_r, bool gqa) {
+  if (gqa) return prefill_lds_kernel<DV, 0, true, KS>;
+  if (d_r == 0) return prefill_lds_kernel<DV, 0, false, KS>;
+  if (d_r <= 16) return prefill_lds_kernel<DV, 1, false, KS>;
+  if (d_r <= 32) return prefill_lds_kernel<DV, 2, false, KS>;
+  return prefill_lds_kernel<DV, 4, false, KS>;
+}
+
+PrefillFn pick_prefill_lds(int dv, int d_r, bool gqa, int ks) {
+  if (dv == 128) return ks == 2 ? pick_prefill_lds_nrc<128, 2>(d_r, gqa) : pick_prefill_lds_nrc<128, 1>(d_r, gqa);
+  return ks == 2 ? pick_prefill_lds_nrc<64, 2>(d_r, gqa) : pick_prefill_lds_nrc<64, 1>(d_r, gqa);
+}
+
 
 template <int HPG, int DV>
 PrefillFn pick_prefill_nrc(int d_r, bool gqa) {
@@ -783,52 +929,50 @@ PrefillFn pick_prefill(int hpg, int dv, int d_r, bool gqa) {
   return nullptr;
 }
 
-template <int HPG, int DV>
-PrefillFn pick_prefill_vt_nrc(int d_r) {
-  if (d_r == 0) return prefill_vt_kernel<HPG, DV, 0, false, false>;
-  if (d_r <= 16) return prefill_vt_kernel<HPG, DV, 1, false, true>;
-  if (d_r <= 32) return prefill_vt_kernel<HPG, DV, 1, false, false>;
-  return nullptr;                              // two positional chunks: the tile-split kernel
-}
-
-PrefillFn pick_prefill_vt(int hpg, int dv, int d_r, bool gqa) {
-  if (dv != 128) return nullptr;               // d_v = 64: the tile-split kernel (measured faster)
-  switch (hpg) {
-    case 1: return gqa ? prefill_vt_kernel<1, 128, 0, true, false> : pick_prefill_vt_nrc<1, 128>(d_r);
-    case 2: return gqa ? prefill_vt_kernel<2, 128, 0, true, false> : pick_prefill_vt_nrc<2, 128>(d_r);
-    case 4: return gqa ? prefill_vt_kernel<4, 128, 0, true, false> : pick_prefill_vt_nrc<4, 128>(d_r);
-    case 8: return gqa ? prefill_vt_kernel<8, 128, 0, true, false> : pick_prefill_vt_nrc<8, 128>(d_r);
-  }
-  return nullptr;
-}
-
-// The columns-per-wave kernel has a quarter of the workgroups of the
-// tile-split one; it wins once they fill the GPU a few times over: from
-// two per CU (H/G <= 4) or four per CU (H/G = 8), measured on prompts of
-// 1K-16K tokens at d_v = 128.
-bool prefer_prefill_vt(const gva_dims* d, int n_new, bool gqa) {
+// Which kernel a prompt takes: the sets of four waves per workgroup of
+// prefill_lds_kernel, or 0 for the tile-split kernel.  By the workgroups of
+// 128 columns against the CUs:
+//  - two per CU and more: one set (two workgroups per CU; 2048 tokens at H32
+//    G8 d 128, 512 workgroups: 81 us, 92 with two sets);
+//  - from 3/4 per CU: two sets, so that each SIMD has two waves (H16 G4 d 64,
+//    2048 tokens, 256 workgroups: 41 us, 48 with one set, 50 tile-split; H32
+//    G8, 768 rows after 8000, 192 workgroups: 142, 165, 159);
+//  - fewer: the tile-split kernel, whose workgroups are a half to an eighth
+//    the size and split the keys over the four waves (H32 G8, 512 rows after
+//    8000, 128 workgroups: 110 us, 133 with two sets; 64 rows after 8000: 68
+//    and 125) -- for the baseline at d_v = 128, whose tile-split workgroups
+//    hold only 16 columns, below 1/2 (256 rows after 8000: 70 and 111; 768:
+//    188 and 125).  Caches of at most 1024 rows keep the one-set kernel: a
+//    workgroup's chain of tiles is then short, and the one launch with the
+//    absorption inside it is what counts (512 tokens, 128 workgroups: 29 and
+//    36 us).
+int prefill_sets(const gva_dims* d, int n_new, bool gqa) {
   const int hpg = d->n_heads / d->n_groups;
-  const int qb = kWaves * prefill_vt_cols(d->d_v, gqa) / hpg;   // positions per workgroup
-  if (qb < 1) return false;
-  const long long qblocks = (n_new + qb - 1) / qb;
-  const long long items = (long long)d->batch * d->n_groups * qblocks;
-  return items >= (hpg >= 8 ? 4LL : 2LL) * device_cu_count();
+  if (hpg > 8) return 0;                       // no kernel takes it
+  const int rows = kPrefillCols / hpg;         // positions per workgroup
+  const long long items = (long long)d->batch * d->n_groups * ((n_new + rows - 1) / rows);
+  const long long n_cu = device_cu_count();
+  if (items >= 2 * n_cu) return 1;
+  if (4 * items >= (gqa && d->d_v >= 128 ? 2 : 3) * n_cu) return 2;
+  return d->t_max <= 1024 ? 1 : 0;
 }
 
-// The launch behind gva_prefill_attention and, with k_gqa given,
+// The launch behind gva_prefill_attention, gva_prefill (raw query q and maps
+// m in place of q_abs and q_rot) and, with k_gqa given,
 // gva_gqa_prefill_attention.
-int prefill_impl(const gva_dims* dims, int32_t n_new, const float* q_abs, const float* q_rot,
-                 const void* v_cache, const void* kr_cache, const void* k_gqa, const int32_t* lens,
-                 float* o, float* lse, void* stream) {
+int prefill_impl(const gva_dims* dims, int32_t n_new, const float* q_abs, const float* q_rot, const void* q,
+                 const void* m, const void* v_cache, const void* kr_cache, const void* k_gqa, const int32_t* lens,
+                 float* o, float* lse, void* stream, bool launch = true) {
   int st = check_dims(dims);
   if (st != GVA_OK) return st;
-  const bool gqa = k_gqa != nullptr;
+  const bool gqa = k_gqa != nullptr, fused = q != nullptr;
   const int d_r = gqa ? 0 : dims->d_r;
   if (n_new < 1 || n_new > dims->t_max) return GVA_ERR_INVALID_ARG;
-  if (!q_abs || !v_cache || !lens || !o || !lse) return GVA_ERR_INVALID_ARG;
-  if (d_r > 0 && (!q_rot || !kr_cache)) return GVA_ERR_INVALID_ARG;
-  if (!aligned(q_abs, 16) || !aligned(v_cache, 16) || !aligned(lens, 4) || !aligned(o, 16) ||
-      !aligned(lse, 4) || (d_r > 0 && (!aligned(q_rot, 16) || !aligned(kr_cache, 16))) ||
+  if (!v_cache || !lens || !o || !lse) return GVA_ERR_INVALID_ARG;
+  if (fused ? !m : (!q_abs || (d_r > 0 && !q_rot))) return GVA_ERR_INVALID_ARG;
+  if (d_r > 0 && !kr_cache) return GVA_ERR_INVALID_ARG;
+  if (!aligned(q_abs, 16) || !aligned(q, 16) || !aligned(m, 16) || !aligned(v_cache, 16) || !aligned(lens, 4) ||
+      !aligned(o, 16) || !aligned(lse, 4) || (d_r > 0 && (!aligned(q_rot, 16) || !aligned(kr_cache, 16))) ||
       (gqa && !aligned(k_gqa, 16)))
     return GVA_ERR_INVALID_ARG;
   if (dims->dtype != GVA_DTYPE_BF16) return GVA_ERR_UNSUPPORTED;
@@ -836,17 +980,18 @@ int prefill_impl(const gva_dims* dims, int32_t n_new, const float* q_abs, const 
   if (st != GVA_OK) return st;
   if (d_r % 8 != 0 || d_r > 64) return GVA_ERR_UNSUPPORTED;
   const int hpg = dims->n_heads / dims->n_groups;
-  // columns per wave where it has a kernel (d_v = 128; GVA with d_r <= 32,
-  // or the GQA baseline) and the grid is large enough, else the tile-split
-  // kernel (d_v = 64, two positional chunks, short prompts)
-  PrefillFn fn = prefer_prefill_vt(dims, n_new, gqa) ? pick_prefill_vt(hpg, dims->d_v, d_r, gqa) : nullptr;
-  const bool per_wave = fn != nullptr;
-  if (!per_wave) fn = pick_prefill(hpg, dims->d_v, d_r, gqa);
+  if (hpg != 1 && hpg != 2 && hpg != 4 && hpg != 8) return GVA_ERR_UNSUPPORTED;
+  if (dims->d_v != 64 && dims->d_v != 128) return GVA_ERR_UNSUPPORTED;
+  const int sets = prefill_sets(dims, n_new, gqa);
+  if (fused && sets == 0) return GVA_ERR_UNSUPPORTED;
+  const PrefillFn fn = sets > 0 ? pick_prefill_lds(dims->d_v, d_r, gqa, sets) : pick_prefill(hpg, dims->d_v, d_r, gqa);
   if (fn == nullptr) return GVA_ERR_UNSUPPORTED;
-  const int qb_rows = (per_wave ? kWaves * prefill_vt_cols(dims->d_v, gqa) : prefill_cols(dims->d_v, gqa)) / hpg;
+  const int qb_rows = (sets > 0 ? kPrefillCols : prefill_cols(dims->d_v, gqa)) / hpg;
   const long long n_qblocks = (n_new + qb_rows - 1) / qb_rows;
   const long long n_items = (long long)dims->batch * dims->n_groups * n_qblocks;
   if (n_items > 0x7FFFFFFFLL) return GVA_ERR_UNSUPPORTED;
+
+  if (!launch) return GVA_OK;
 
   PrefillParams p{};
   memset(&p, 0, sizeof(p));
@@ -855,6 +1000,10 @@ int prefill_impl(const gva_dims* dims, int32_t n_new, const float* q_abs, const 
   p.v = v_cache;
   p.kr = kr_cache;
   p.k_gqa = k_gqa;
+  p.q = q;
+  p.m = m;
+  p.d_c = dims->d_c;
+  fill_inv_freq(dims, p.inv_freq);
   p.lens = lens;
   p.o = o;
   p.lse = lse;
@@ -871,11 +1020,24 @@ int prefill_impl(const gva_dims* dims, int32_t n_new, const float* q_abs, const 
   } else {
     p.scale_log2 = scale_log2(dims);
   }
-  hipLaunchKernelGGL(fn, dim3((unsigned)n_items), dim3(kThreads), 0, static_cast<hipStream_t>(stream), p);
+  hipLaunchKernelGGL(fn, dim3((unsigned)n_items), dim3(sets == 2 ? 2 * kThreads : kThreads), 0, static_cast<hipStream_t>(stream), p);
   return launch_status();
 }
 
-// The append behind gva_append_kv and, with paging given, gva_paged_append_kv.
+// Where gva_prefill's two launches keep the absorbed queries; bytes = 0 where
+// the absorption is fused.
+struct PrefillLayout {
+  size_t q_rot, bytes;
+};
+
+void prefill_layout(const gva_dims* d, int n_new, PrefillLayout& L) {
+  L = PrefillLayout{0, 0};
+  if (prefill_sets(d, n_new, false) > 0) return;
+  const size_t rows = (size_t)d->batch * n_new * d->n_heads;
+  L.q_rot = (rows * d->d_v * 4 + 255) / 256 * 256;
+  L.bytes = L.q_rot + (rows * d->d_r * 4 + 255) / 256 * 256;
+}
+
 }  // namespace
 
 extern "C" {
@@ -883,14 +1045,50 @@ extern "C" {
 int gva_prefill_attention(const gva_dims* dims, int32_t n_new, const float* q_abs, const float* q_rot,
                           const void* v_cache, const void* kr_cache, const int32_t* lens, float* o,
                           float* lse, void* stream) {
-  return prefill_impl(dims, n_new, q_abs, q_rot, v_cache, kr_cache, nullptr, lens, o, lse, stream);
+  return prefill_impl(dims, n_new, q_abs, q_rot, nullptr, nullptr, v_cache, kr_cache, nullptr, lens, o, lse, stream);
+}
+
+int gva_prefill_workspace_size(const gva_dims* dims, int32_t n_new, size_t* bytes) {
+  if (bytes == nullptr) return GVA_ERR_INVALID_ARG;
+  const int st = check_dims(dims);
+  if (st != GVA_OK) return st;
+  if (n_new < 1 || n_new > dims->t_max) return GVA_ERR_INVALID_ARG;
+  PrefillLayout L;
+  prefill_layout(dims, n_new, L);
+  *bytes = L.bytes;
+  return GVA_OK;
+}
+
+int gva_prefill(const gva_dims* dims, int32_t n_new, const void* q, const void* m, const void* v_cache,
+                const void* kr_cache, const int32_t* lens, void* workspace, size_t workspace_bytes, float* o,
+                float* lse, void* stream) {
+  int st = check_dims(dims);
+  if (st != GVA_OK) return st;
+  if (n_new < 1 || n_new > dims->t_max) return GVA_ERR_INVALID_ARG;
+  if (!q || !m || !v_cache || !lens || !o || !lse) return GVA_ERR_INVALID_ARG;
+  // the absorption's bounds hold for both forms
+  const long long rows = (long long)dims->batch * n_new;
+  if (rows > (1LL << 20) || rows * dims->n_heads > 0x7FFFFFFFLL || dims->d_c % 32 != 0) return GVA_ERR_UNSUPPORTED;
+  PrefillLayout L;
+  prefill_layout(dims, n_new, L);
+  if (L.bytes == 0)
+    return prefill_impl(dims, n_new, nullptr, nullptr, q, m, v_cache, kr_cache, nullptr, lens, o, lse, stream);
+  if (workspace == nullptr || workspace_bytes < L.bytes || !aligned(workspace, 256)) return GVA_ERR_INVALID_ARG;
+  float* q_abs = static_cast<float*>(workspace);
+  float* q_rot = dims->d_r > 0 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + L.q_rot) : nullptr;
+  // every check of the second launch before the first is enqueued
+  st = prefill_impl(dims, n_new, q_abs, q_rot, nullptr, nullptr, v_cache, kr_cache, nullptr, lens, o, lse, stream, false);
+  if (st != GVA_OK) return st;
+  st = gva_prefill_absorb(dims, n_new, q, m, lens, q_abs, q_rot, stream);
+  if (st != GVA_OK) return st;
+  return prefill_impl(dims, n_new, q_abs, q_rot, nullptr, nullptr, v_cache, kr_cache, nullptr, lens, o, lse, stream);
 }
 
 int gva_gqa_prefill_attention(const gva_dims* dims, int32_t n_new, const float* q, const void* k_cache,
                               const void* v_cache, const int32_t* lens, float* o, float* lse,
                               void* stream) {
   if (k_cache == nullptr) return GVA_ERR_INVALID_ARG;
-  return prefill_impl(dims, n_new, q, nullptr, v_cache, nullptr, k_cache, lens, o, lse, stream);
+  return prefill_impl(dims, n_new, q, nullptr, nullptr, nullptr, v_cache, nullptr, k_cache, lens, o, lse, stream);
 }
 
 }  // extern "C"

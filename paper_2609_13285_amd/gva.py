@@ -25,8 +25,8 @@ GVA_MAX_SPLITS = 256
 EXPORTS = ("gva_append_kv", "gva_absorb_query", "gva_decode_attention", "gva_combine",
            "gva_gqa_decode_attention", "gva_paged_append_kv", "gva_paged_decode_attention",
            "gva_rope_decode_attention", "gva_prefill_absorb", "gva_prefill_attention",
-           "gva_gqa_prefill_attention", "gva_pick_splits", "gva_prefer_fused", "gva_status_string",
-           "gva_version", "gva_decode_workspace_size", "gva_decode_step", "gva_decode_step_static")
+           "gva_gqa_prefill_attention", "gva_prefill_workspace_size", "gva_prefill", "gva_pick_splits",
+           "gva_prefer_fused", "gva_status_string", "gva_version", "gva_decode_workspace_size", "gva_decode_step", "gva_decode_step_static")
 GVA_MAX_PAGES = 4096
 PROBE_EXPORTS = ("gva_probe_read",)      # include/gva_probe.h
 
@@ -77,6 +77,8 @@ def lib() -> ctypes.CDLL:
         L.gva_rope_decode_attention.argtypes = [D, P, P, P, P, I32, I32, P, P, P]
         L.gva_prefill_absorb.argtypes = [D, I32, P, P, P, P, P, P]
         L.gva_prefill_attention.argtypes = [D, I32, P, P, P, P, P, P, P, P]
+        L.gva_prefill_workspace_size.argtypes = [D, I32, ctypes.POINTER(ctypes.c_size_t)]
+        L.gva_prefill.argtypes = [D, I32, P, P, P, P, P, P, ctypes.c_size_t, P, P, P]
         L.gva_gqa_prefill_attention.argtypes = [D, I32, P, P, P, P, P, P, P]
         PG = ctypes.POINTER(GvaPaging)
         L.gva_paged_append_kv.argtypes = [D, PG, P, P, P, P, P, P, P, I32, P]
@@ -93,7 +95,8 @@ def lib() -> ctypes.CDLL:
         for name in ("gva_append_kv", "gva_absorb_query", "gva_decode_attention", "gva_combine",
                      "gva_gqa_decode_attention", "gva_paged_append_kv", "gva_paged_decode_attention",
                      "gva_rope_decode_attention", "gva_prefill_absorb", "gva_prefill_attention",
-                     "gva_gqa_prefill_attention", "gva_pick_splits", "gva_version", "gva_probe_read",
+                     "gva_gqa_prefill_attention", "gva_prefill_workspace_size", "gva_prefill",
+                     "gva_pick_splits", "gva_version", "gva_probe_read",
                      "gva_decode_workspace_size", "gva_decode_step", "gva_decode_step_static"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
@@ -412,6 +415,36 @@ def gva_prefill_attention(dims: GvaDims, n_new: int, q_abs, q_rot, v_cache, kr_c
     _check("gva_prefill_attention", st)
 
 
+def gva_prefill_workspace_size(dims: GvaDims, n_new: int) -> int:
+    """Workspace bytes gva_prefill needs for this prompt on the current device."""
+    n = ctypes.c_size_t(0)
+    _check("gva_prefill_workspace_size",
+           lib().gva_prefill_workspace_size(ctypes.byref(dims), int(n_new), ctypes.byref(n)))
+    return int(n.value)
+
+
+def gva_prefill(dims: GvaDims, n_new: int, q, m, v_cache, kr_cache, lens, o, lse, workspace=None, stream=None):
+    """gva_prefill_absorb and gva_prefill_attention in one call."""
+    d = dims
+    N = int(n_new)
+    dt = d.torch_dtype
+    if workspace is not None and (workspace.dtype != torch.uint8 or workspace.dim() != 1):
+        raise ValueError("workspace must be a 1-D uint8 tensor")
+    st = lib().gva_prefill(
+        ctypes.byref(d), N,
+        _ptr(q, "q", dt, (d.batch, N, d.n_heads, d.d_c + d.d_r)),
+        _ptr(m, "m", dt, (d.n_heads, d.d_v, d.d_c)),
+        _ptr(v_cache, "v_cache", dt, (d.batch, d.n_groups, d.t_max, d.d_v)),
+        _ptr(kr_cache, "kr_cache", dt, (d.batch, d.t_max, d.d_r)) if d.d_r > 0 else None,
+        _ptr(lens, "lens", torch.int32, (d.batch,)),
+        _ptr(workspace, "workspace"),
+        0 if workspace is None else workspace.numel(),
+        _ptr(o, "o", torch.float32, (d.batch, N, d.n_heads, d.d_v)),
+        _ptr(lse, "lse", torch.float32, (d.batch, N, d.n_heads)),
+        _stream(stream))
+    _check("gva_prefill", st)
+
+
 def gva_gqa_prefill_attention(dims: GvaDims, n_new: int, q, k_cache, v_cache, lens, o, lse, stream=None):
     """The matched-GQA causal prefill: q [B, n_new, H, d_v] fp32."""
     d = dims
@@ -659,13 +692,12 @@ def prefill(dims: GvaDims, q, m, v_cache, kr_cache, lens, stream=None) -> Tuple[
     d = dims
     B, N = q.shape[0], q.shape[1]
     dev = v_cache.device
-    q_abs = torch.empty(B, N, d.n_heads, d.d_v, dtype=torch.float32, device=dev)
-    q_rot = torch.empty(B, N, d.n_heads, d.d_r, dtype=torch.float32, device=dev)
     o = torch.empty(B, N, d.n_heads, d.d_v, dtype=torch.float32, device=dev)
     lse = torch.empty(B, N, d.n_heads, dtype=torch.float32, device=dev)
-    _in_use_on(stream, q_abs, q_rot, o, lse)
-    gva_prefill_absorb(d, N, q, m, lens, q_abs, q_rot, stream=stream)
-    gva_prefill_attention(d, N, q_abs, q_rot, v_cache, kr_cache, lens, o, lse, stream=stream)
+    n = gva_prefill_workspace_size(d, N)
+    ws = torch.empty(n, dtype=torch.uint8, device=dev) if n else None
+    _in_use_on(stream, o, lse, ws)
+    gva_prefill(d, N, q, m, v_cache, kr_cache, lens, o, lse, workspace=ws, stream=stream)
     return o, lse
 
 

@@ -137,6 +137,30 @@ def test_absorb_validation():
     assert lib.gva_absorb_query(None, A, A, A, A, A, None) == gva.GVA_ERR_INVALID_ARG
 
 
+def test_prefill_validation():
+    # the one-call prompt: what the absorption and the attention refuse
+    lib = gva.lib()
+
+    def status(d, n=4, q=A, m=A, v=A, kr=A, lens=A, ws=None, nbytes=0, o=A, lse=A):
+        return lib.gva_prefill(ctypes.byref(d), n, q, m, v, kr, lens, ws, nbytes, o, lse, None)
+
+    d = dims(batch=2, n_heads=8, n_groups=2, t_max=4096)
+    for k in ("q", "m", "v", "kr", "lens", "o", "lse"):
+        assert status(d, ws=A * 256, nbytes=1 << 30, **{k: None}) == gva.GVA_ERR_INVALID_ARG, k
+    assert status(d, n=0) == gva.GVA_ERR_INVALID_ARG and status(d, n=4097) == gva.GVA_ERR_INVALID_ARG
+    # few workgroups over a long cache: the absorbed queries go to a workspace
+    need = gva.gva_prefill_workspace_size(d, 4)
+    assert need >= 2 * 4 * 8 * (d.d_v + d.d_r) * 4
+    assert status(d) == gva.GVA_ERR_INVALID_ARG
+    assert status(d, ws=A * 256, nbytes=need - 1) == gva.GVA_ERR_INVALID_ARG
+    assert status(d, ws=A * 256 + 16, nbytes=need) == gva.GVA_ERR_INVALID_ARG
+    # unsupported on either route
+    big = dict(batch=64, n_heads=64, n_groups=8, t_max=512)
+    for kw in (dict(d_c=48), dict(d_v=96), dict(dtype="f32"), dict(d_r=12), dict(n_heads=128)):
+        assert status(dims(**{**big, **kw}), n=512, ws=A * 256, nbytes=1 << 40) == gva.GVA_ERR_UNSUPPORTED, kw
+    assert gva.gva_prefill_workspace_size(dims(**big), 512) == 0
+
+
 def test_pick_splits_is_host_only_and_bounded():
     d = dims(batch=32, n_heads=32, n_groups=8, t_max=8192)
     assert gva.gva_pick_splits(d, 8192, 0, 256) == (1, 0)       # 256 streams fill 256 CUs

@@ -1290,6 +1290,59 @@ def test_gqa_prefill_columns_per_wave_matches_oracle(B, hpg, G, N, prefix):
     _prefill_check(o[:, idx], lse[:, idx], o_ref, lse_ref, f"gqa prefill per wave hpg{hpg} G{G} N{N}")
 
 
+# Shapes on the edges of the kernel whose waves share key tiles through LDS
+# (128 columns per workgroup): (B, H/G, G, d_v, d_c, d_r, N, rows before the
+# prompt of the first sequence, sets of waves the grid takes).  A last block
+# of one and of all but one position, lengths off every tile, each number of
+# positional chunks with and without a half-used last one, d_c off d_v and
+# off the 64 columns of an absorption round, and sequences shorter than the
+# prompt.
+PREFILL_LDS_CASES = [
+    (8, 8, 4, 64, 96, 24, 193, 30, 2),
+    (8, 4, 8, 128, 64, 40, 255, 61, 1),
+    (16, 1, 16, 64, 64, 8, 70, 5, 2),
+    (16, 2, 16, 128, 128, 16, 65, 40, 1),
+    (8, 4, 8, 64, 32, 0, 225, 0, 1),
+    (8, 8, 8, 128, 160, 32, 100, -30, 2),
+    (4, 4, 8, 128, 128, 64, 193, 100, 2),
+]
+
+
+@pytest.mark.parametrize("B,hpg,G,dv,dc,dr,N,prefix,sets", PREFILL_LDS_CASES)
+def test_prefill_shared_tiles_matches_oracle(B, hpg, G, dv, dc, dr, N, prefix, sets):
+    # the fused call and the two calls with the absorption apart, both
+    # against the oracle (PREFILL_QUALITY's derivation holds for both); NaN
+    # behind every length
+    n_cu = gva.device_cu_count()
+    items = B * G * -(-N // (128 // hpg))
+    assert (items >= 2 * n_cu) == (sets == 1) and 4 * items >= 3 * n_cu, "the shape must take this kernel"
+    T = -(-(N + max(prefix, 0)) // 16) * 16
+    w = gva_inputs.Workload("prefill_lds", B, T, hpg * G, G, dv, dc, dr, dtype="bf16")
+    lens = torch.tensor([max(1, N + prefix - 3 * b) for b in range(B)], dtype=torch.int32)
+    inp = gva_inputs.make_inputs(w, 59, lens=lens)
+    for b, L in enumerate(lens.tolist()):
+        inp["v"][b, :, L:] = float("nan")
+        inp["kr"][b, L:] = float("nan")
+    q = gva_inputs.prefill_queries(w, 59, N)
+    label = f"prefill lds B{B} hpg{hpg} G{G} d{dv}/{dc}/{dr} N{N}"
+    note(f"{label}: oracle")
+    o_ref, lse_ref = oracle.prefill(q, inp["m"], inp["v"], inp["kr"], lens, rope_base=w.rope_base)
+    dev = upload({k: inp[k] for k in ("m", "v", "kr", "lens")})
+    d = dims_of(w)
+    assert gva.gva_prefill_workspace_size(d, N) == 0
+    note(f"{label}: GPU, fused")
+    o, lse = gva.prefill(d, q.cuda(), dev["m"], dev["v"], dev["kr"], dev["lens"])
+    _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label + " fused")
+    note(f"{label}: GPU, two calls")
+    qa = torch.empty(B, N, w.n_heads, dv, dtype=torch.float32, device="cuda")
+    qr = torch.empty(B, N, w.n_heads, dr, dtype=torch.float32, device="cuda")
+    o.fill_(float("nan"))
+    lse.fill_(float("nan"))
+    gva.gva_prefill_absorb(d, N, q.cuda(), dev["m"], dev["lens"], qa, qr)
+    gva.gva_prefill_attention(d, N, qa, qr, dev["v"], dev["kr"], dev["lens"], o, lse)
+    _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label + " two calls")
+
+
 def test_prefill_after_append_of_the_prompt():
     # Algorithm 1's append for every prompt row (gva_append_kv), then the
     # prefill over the appended caches, against the oracle doing the same
