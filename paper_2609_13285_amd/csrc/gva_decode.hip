@@ -14,7 +14,7 @@
 //                        positional-key rows of one (sequence, group, split)
 //                        on the matrix cores, online softmax, optional fused
 //                        absorption prologue
-//   decode_f32_kernel    fp32-storage variant on the vector ALUs
+//   decode_f32_kernel    fp32-storage variant on the fp32 matrix products
 //   combine_kernel       log-sum-exp merge of the split partials
 //
 // Cache layout (MFMA-native).  Each (sequence, group) value stream and each
@@ -862,240 +862,372 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves ? 2 : 1) decode_bf16_ker
 }
 
 // ========================================================== decode (f32)
-// Vector-ALU variant for fp32 storage.  Per 64-row tile a wave first scores
-// one row per lane, then accumulates the weighted rows with one output
-// element per lane.
+// fp32 storage on the fp32 matrix products (v_mfma 16x16x4 f32: full fp32
+// multiply-adds), built like the bf16 kernel: a workgroup owns one
+// (b, g, split), its waves take interleaved 16-row tiles and keep DEPTH of
+// them in registers.  In the tiled layout a wave's 16-byte load gives lane
+// (n, qd) = (lane % 16, lane / 16) four columns 4 qd + e of row n, so element
+// e of every lane is the A operand of one product over columns
+// {4 qd + e}, and the query's B operand is the same four entries of head n.
+//   scores  S^T[t][n] += V[t][4 qd + e] q[n][4 qd + e]      e = 0..3 per chunk
+//   P.V     O^T[i][n] += V^T[i][4 qd + j] P[4 qd + j][n]    j = 0..3 per block
+// The scores come back with rows 4 qd + j in register j, the B operand of
+// P.V as they are; V^T goes through LDS (a tile of the wave's own, rows
+// padded by 16 bytes so that neither side conflicts), which moves bits and
+// costs less than products with an identity would (4 of 16 x 16 x 4 per
+// block).  NC and NRC are d_v and d_r in 16-column chunks, rounded up: pieces
+// past either re-read a valid one against a zero query and their outputs are
+// not written.
+// The matrix cores take 256 cycles per 16 x 16 block of a tile (9.8 TB/s of
+// rows at 2.4 GHz), whatever the heads per group, so the kernel is bound by
+// latency at the sizes fp32 is used at.  The kernel it replaced scored one
+// row per lane on the vector units with every query entry read from LDS, and
+// read each value row a second time for P.V.  Step times, then and now: B1
+// T256 H8 G2 d 64/16 45.0 -> 9.6 us; B8 of up to 4096 rows, H16 G4 d 64/16,
+// 87.2 -> 18.2 us; B32 T4096 H32 G8 d 128/16 (545 MB)
+// 1051 -> 104 us, 5.2 TB/s.
 constexpr int kF32MaxHpg = 8;
 constexpr int kF32MaxDv = 256;
 constexpr int kF32MaxDr = 64;
+constexpr int kF32TileRows = 16;
 
-__global__ void __launch_bounds__(kThreads) decode_f32_kernel(DecodeParams p) {
-  __shared__ float qs[kF32MaxHpg][kF32MaxDv + 1];
-  __shared__ float qr[kF32MaxHpg][kF32MaxDr];
-  __shared__ float pb[kWaves][64][kF32MaxHpg];
-  __shared__ float red_ml[kWaves][kF32MaxHpg][2];
-  __shared__ float red_o[kWaves][kF32MaxHpg][kF32MaxDv];
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <int NC, int NRC, int NW>
+struct F32Cfg {
+  static constexpr int PITCH = 16 * NC + 4;                  // floats per padded LDS row
+  static constexpr int QR_PITCH = 16 * NRC + 4;
+  static constexpr int DEPTH = NC <= 4 ? 4 : (NC <= 8 && NRC == 1 ? 3 : 2);
+  static constexpr int AR = NC <= 4 ? 8 : 16;                // absorption: loads of four map rows per round
+  static constexpr int LDS_PRO = kF32MaxHpg * (PITCH + QR_PITCH);
+  static constexpr int LDS_TR = NW * 16 * PITCH;
+  static constexpr int LDS_RED = NW * kF32MaxHpg * PITCH;    // per (wave, head): o, m, l
+  static constexpr int LDS_A = LDS_PRO > LDS_TR ? LDS_PRO : LDS_TR;
+  static constexpr int LDS_FLOATS = LDS_A > LDS_RED ? LDS_A : LDS_RED;
+};
+
+template <int NC, int NRC, int NW>
+__global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1) decode_f32_kernel(DecodeParams p) {
+  using Cfg = F32Cfg<NC, NRC, NW>;
+  constexpr int NT = 64 * NW, DEPTH = Cfg::DEPTH, AR = Cfg::AR, PITCH = Cfg::PITCH, QRP = Cfg::QR_PITCH;
+  const DecodeArgs a = p.a;
+  const bool fused = a.q != nullptr;
+  asm volatile("" ::"s"(a.B), "s"(a.H), "s"(a.G), "s"(a.S), "s"(a.t_max), "s"(a.split_rows), "s"(a.d_r), "s"(a.d_c),
+               "s"(a.d_v), "s"(a.lens), "s"(a.v_new), "s"(a.kr_new), "s"(a.q), "s"(a.m), "s"(a.q_abs), "s"(a.q_rot),
+               "s"(gridDim.x)
+               : "memory");                    // one round trip for the arguments, as request_args
+  __shared__ __attribute__((aligned(16))) float lds[Cfg::LDS_FLOATS];
+  __shared__ __attribute__((aligned(16))) float prow[16 * NC + 16 * NRC];   // the current token's row
 
   int b, s, g;
   bool empty_slot;
-  if (!work_item(p.a, b, s, g, empty_slot)) return;   // grid padding
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int hpg = p.a.H / p.a.G, h0 = g * hpg;
-  const int DV = p.a.d_v, DR = p.a.d_r;
-  const int L = clamp_len(p.a.lens, b, p.a.t_max);
-  int r0, r1;
-  split_rows(L, p.a.S, p.a.split_rows, s, r0, r1);
-  if (r0 >= r1 && s > 0) {                     // an empty split past the first: lse only
-    if (tid < hpg) p.a.lse_part[((int64_t)b * p.a.H + h0 + tid) * p.a.S + s] = -INFINITY;
+  if (!work_item(a, b, s, g, empty_slot)) return;   // grid padding
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, qd = lane >> 4;
+  const int hpg = a.H / a.G, h0 = g * hpg;
+  const int DV = a.d_v, DR = a.d_r;
+  const int len_b = *(const __attribute__((address_space(4))) int32_t*)(a.lens + b);
+  if (empty_slot && s > 0) {                   // bounded chunks: a split with no rows
+    if (tid < hpg) a.lse_part[((int64_t)b * a.H + h0 + tid) * a.S + s] = -INFINITY;
     return;
   }
-  const bool pending = p.a.v_new != nullptr && L > 0 && r0 <= L - 1 && L - 1 < r1;
+
+  // ---- loads that do not depend on the length: the current token's rows,
+  // then the first round of the absorption
+  f32x4 pend_piece = {0.f, 0.f, 0.f, 0.f};
+  float pk0 = 0.f, pk1 = 0.f;
+  double kfreq = 0.0;
+  if (a.v_new != nullptr) {
+    if (tid < DV / 4)
+      pend_piece = *(reinterpret_cast<const f32x4*>(static_cast<const float*>(a.v_new) + ((int64_t)b * a.G + g) * DV) + tid);
+    if (tid < DR / 2) {
+      const float* kn = static_cast<const float*>(a.kr_new) + (int64_t)b * DR + 2 * tid;
+      pk0 = kn[0];
+      pk1 = kn[1];
+      kfreq = p.inv_freq[tid];
+    }
+  }
+  // Fused absorption: a job is 4 AR rows of one head's map, wave w taking
+  // jobs w, w + NW, ...; a load covers four rows of 64 columns (16 lanes of
+  // 16 bytes each), a round AR loads.  Rows that are not whole 16-byte
+  // pieces (d_c not a multiple of 4) are read element by element.
+  const int W = a.d_c + DR;
+  const bool whole = (a.d_c & 3) == 0;
+  const int per_head = (DV + 4 * AR - 1) / (4 * AR);
+  const int njobs = fused ? hpg * per_head : 0;
+  const int nseg = (a.d_c + 63) / 64;
+  f32x4 am[AR], xq = {0.f, 0.f, 0.f, 0.f};
+  auto load4 = [&](const float* row, int col) __attribute__((always_inline)) {
+    if (whole) return *reinterpret_cast<const f32x4*>(row + min(col, a.d_c - 4));
+    f32x4 x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = row[min(col + e, a.d_c - 1)];
+    return x;
+  };
+  auto load_round = [&](int job, int seg) __attribute__((always_inline)) {    // columns past d_c: valid ones, against zeros of the query
+    const int hl = job / per_head, i0 = (job % per_head) * 4 * AR + qd;
+    const int col = 64 * seg + 4 * n;
+    xq = load4(static_cast<const float*>(a.q) + ((int64_t)b * a.H + h0 + hl) * W, col);
+    const float* mh = static_cast<const float*>(a.m) + (int64_t)(h0 + hl) * DV * a.d_c;
+#pragma unroll
+    for (int r = 0; r < AR; ++r) am[r] = load4(mh + (int64_t)min(i0 + 4 * r, DV - 1) * a.d_c, col);
+  };
+  const int npair = DR / 2;
+  const int ptid = NT - 1 - tid;
+  const bool has_pair = fused && ptid < hpg * npair;
+  const int pair_h = npair > 0 ? ptid / npair : 0, pair_i = npair > 0 ? ptid % npair : 0;
+  float rq0 = 0.f, rq1 = 0.f;
+  double qfreq = 0.0;
+  if (has_pair) {
+    const float* qp = static_cast<const float*>(a.q) + ((int64_t)b * a.H + h0 + pair_h) * W + a.d_c + 2 * pair_i;
+    rq0 = qp[0];
+    rq1 = qp[1];
+    qfreq = p.inv_freq[pair_i];
+  }
+  if (w < njobs && nseg > 0) load_round(w, 0);
+  __builtin_amdgcn_sched_barrier(0);
+
+  const int L = len_b < 0 ? 0 : (len_b > a.t_max ? a.t_max : len_b);
+  int r0, r1;
+  split_rows(L, a.S, a.split_rows, s, r0, r1);
+  if (r0 >= r1 && s > 0) {                     // an empty split past the first: lse only
+    if (tid < hpg) a.lse_part[((int64_t)b * a.H + h0 + tid) * a.S + s] = -INFINITY;
+    return;
+  }
+  const bool pending = a.v_new != nullptr && L > 0 && r0 <= L - 1 && L - 1 < r1;
   if (pending) r1 = L - 1;
+  const int r1c = (r1 + kLayoutRows - 1) / kLayoutRows * kLayoutRows;
 
-  if (p.a.fused) {
-    const float* qg = static_cast<const float*>(p.a.q);
-    const float* mg = static_cast<const float*>(p.a.m);
-    const int W = p.a.d_c + DR;
-    for (int idx = tid; idx < hpg * DV; idx += kThreads) {
-      const int hl = idx / DV, i = idx % DV;
-      const float* qrow = qg + ((int64_t)b * p.a.H + h0 + hl) * W;
-      const float* mrow = mg + ((int64_t)(h0 + hl) * DV + i) * p.a.d_c;
-      const float a = dot_f32(qrow, mrow, p.a.d_c);
-      qs[hl][i] = a * p.a.scale_log2;
-    }
-    const int L1 = L > 0 ? L - 1 : 0;
-    for (int idx = tid; idx < hpg * (DR / 2); idx += kThreads) {
-      const int hl = idx / (DR / 2), i = idx % (DR / 2);
-      const float* qrow = qg + ((int64_t)b * p.a.H + h0 + hl) * W + p.a.d_c;
-      double y0, y1;
-      rotate_pair(qrow[2 * i], qrow[2 * i + 1], (double)L1 * p.inv_freq[i], y0, y1);
-      qr[hl][2 * i] = (float)(y0 * (double)p.a.scale_log2);
-      qr[hl][2 * i + 1] = (float)(y1 * (double)p.a.scale_log2);
-    }
-  } else {
-    for (int idx = tid; idx < hpg * DV; idx += kThreads) {
-      const int hl = idx / DV, i = idx % DV;
-      qs[hl][i] = p.a.q_abs[((int64_t)b * p.a.H + h0 + hl) * DV + i] * p.a.scale_log2;
-    }
-    for (int idx = tid; idx < hpg * DR; idx += kThreads) {
-      const int hl = idx / DR, j = idx % DR;
-      qr[hl][j] = p.a.q_rot[((int64_t)b * p.a.H + h0 + hl) * DR + j] * p.a.scale_log2;
-    }
-  }
-  __syncthreads();
-
-  const float* vb = static_cast<const float*>(p.a.v) + ((int64_t)b * p.a.G + g) * p.a.t_max * DV;
-  const float* kb = static_cast<const float*>(p.a.kr) + (int64_t)b * p.a.t_max * DR;
-  float m_run[kF32MaxHpg], l_run[kF32MaxHpg], acc[kF32MaxHpg][4];
+  // ---- streaming setup, as in the bf16 kernel: descriptors that end at the
+  // split's last layout tile, so prefetches past it read zeros unconditionally
+  const float* vbase = static_cast<const float*>(a.v) + ((int64_t)b * a.G + g) * a.t_max * DV;
+  const float* kbase = static_cast<const float*>(a.kr) + (int64_t)b * a.t_max * DR;
+  const __amdgpu_buffer_rsrc_t vres =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vbase), (short)0, r1c * DV * 4, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t kres =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(kbase), (short)0, r1c * DR * 4, kBufferWord3);
+  int v_lane[NC], k_lane[NRC];
 #pragma unroll
-  for (int h = 0; h < kF32MaxHpg; ++h) {
-    m_run[h] = -INFINITY;
-    l_run[h] = 0.f;
+  for (int c = 0; c < NC; ++c) v_lane[c] = min(4 * c + qd, DV / 4 - 1) * 256 + n * 16;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc[h][u] = 0.f;
-  }
-  const int ntiles = (r1 - r0 + 63) / 64;
-  const int iters = (ntiles + kWaves - 1) / kWaves;
-  for (int it = 0; it < iters; ++it) {
-    const int tile = w + kWaves * it;
-    const int row0 = r0 + 64 * tile;
-    const bool has = tile < ntiles;
-    if (has) {
-      const int t = row0 + lane;
-      const bool valid = t < r1;
-      float sc[kF32MaxHpg];
+  for (int c = 0; c < NRC; ++c) k_lane[c] = max(min(4 * c + qd, DR / 4 - 1), 0) * 256 + n * 16;
+  struct TileF {
+    f32x4 v[NC], k[NRC];
+  };
+  const int ntiles = (r1 - r0 + kF32TileRows - 1) / kF32TileRows;
+  const int my_tiles = ntiles > w ? (ntiles - w + NW - 1) / NW : 0;
+  auto tile_row = [&](int j) { return r0 + (w + NW * j) * kF32TileRows; };
+  auto load_tile = [&](TileF& t, int row0) __attribute__((always_inline)) {
+    const int lt = row0 / kLayoutRows;
 #pragma unroll
-      for (int h = 0; h < kF32MaxHpg; ++h) sc[h] = 0.f;
-      if (valid) {
-        // the row's 16-byte pieces (4 floats each, contiguous in the tiled
-        // layout), eight requested per step
-        const float* vrow = vb + tiled_off<float>(t, 0, DV);
-        const int npc = DV / 4;
-        for (int pc0 = 0; pc0 < npc; pc0 += 8) {
-          f32x4 vv[8];
+    for (int c = 0; c < NC; ++c)
+      t.v[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(vres, v_lane[c], lt * DV * 64, kAuxNT));
 #pragma unroll
-          for (int u = 0; u < 8; ++u)
-            vv[u] = pc0 + u < npc ? *reinterpret_cast<const f32x4*>(vrow + (int64_t)(pc0 + u) * 4 * kLayoutRows)
-                                  : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < NRC; ++c)
+      t.k[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kres, k_lane[c], lt * DR * 64, 0));
+  };
+  TileF buf[DEPTH];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            if (pc0 + u >= npc) break;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int i = 4 * (pc0 + u) + e;
-#pragma unroll
-              for (int h = 0; h < kF32MaxHpg; ++h)
-                if (h < hpg) sc[h] = fmaf(qs[h][i], vv[u][e], sc[h]);
-            }
-          }
-        }
-        const float* krow = kb + tiled_off<float>(t, 0, DR);
-        for (int pc0 = 0; pc0 < DR / 4; pc0 += 8) {
-          f32x4 kv[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-            kv[u] = pc0 + u < DR / 4 ? *reinterpret_cast<const f32x4*>(krow + (int64_t)(pc0 + u) * 4 * kLayoutRows)
-                                     : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            if (pc0 + u >= DR / 4) break;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-              for (int h = 0; h < kF32MaxHpg; ++h)
-                if (h < hpg) sc[h] = fmaf(qr[h][4 * (pc0 + u) + e], kv[u][e], sc[h]);
-          }
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < kF32MaxHpg; ++h) {
-        if (h < hpg) {
-          const float x = valid ? sc[h] : -INFINITY;
-          const float mt = wave_max(x);
-          const float m_new = fmaxf(m_run[h], mt);
-          const float alpha = __builtin_amdgcn_exp2f(m_run[h] - m_new);
-          const float pr = __builtin_amdgcn_exp2f(x - m_new);
-          l_run[h] = l_run[h] * alpha + wave_sum(pr);
-#pragma unroll
-          for (int u = 0; u < 4; ++u) acc[h][u] *= alpha;
-          m_run[h] = m_new;
-          pb[w][lane][h] = pr;
-        }
-      }
-    }
-    __syncthreads();
-    if (has) {
-      const int nrow = r1 - row0 < 64 ? r1 - row0 : 64;
-#pragma unroll 16
-      for (int t = 0; t < nrow; ++t) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = lane + 64 * u;
-          if (i < DV) {
-            const float v = vb[tiled_off<float>(row0 + t, i, DV)];
-#pragma unroll
-            for (int h = 0; h < kF32MaxHpg; ++h)
-              if (h < hpg) acc[h][u] = fmaf(pb[w][t][h], v, acc[h][u]);
-          }
-        }
-      }
-    }
-    __syncthreads();
+  for (int d = 0; d < DEPTH - 1; ++d) {
+    load_tile(buf[d], tile_row(d));
+    __builtin_amdgcn_sched_barrier(0);
   }
 
-  // the pending row (current token), taken from v_new / kr_new with the
-  // rotation and rounding gva_append_kv would store, added by wave 0
+  // ---- absorption (each lane's partial dots, summed over a row's 16 lanes)
+  float* qs = lds;                             // [hpg][PITCH]
+  float* qrs = lds + kF32MaxHpg * PITCH;       // [hpg][QRP]
+  auto absorb_job = [&](int job, bool loaded) __attribute__((always_inline)) {
+    const int hl = job / per_head, i0 = (job % per_head) * 4 * AR + qd;
+    float v[AR];
+#pragma unroll
+    for (int r = 0; r < AR; ++r) v[r] = 0.f;
+    for (int seg = 0; seg < nseg; ++seg) {
+      if (!(loaded && seg == 0)) load_round(job, seg);
+      f32x4 qv;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) qv[e] = 64 * seg + 4 * n + e < a.d_c ? xq[e] : 0.f;
+#pragma unroll
+      for (int r = 0; r < AR; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[r] = fmaf(am[r][e], qv[e], v[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < AR; ++r) {
+      v[r] = sum16(v[r]) * a.scale_log2;
+      if (i0 + 4 * r < DV) qs[hl * PITCH + i0 + 4 * r] = v[r];
+    }
+  };
+  if (w < njobs) absorb_job(w, true);
+  for (int job = w + NW; job < njobs; job += NW) absorb_job(job, false);
+
+  // ---- the current token's row: wave 0 rotates its positional pair (fp64,
+  // rounded once, as append_kernel does), stores the row into the caches (it
+  // is the only reader of row L-1 of the stream in this launch) and stages it
   if (pending && w == 0) {
-    const float* vn = static_cast<const float*>(p.a.v_new) + ((int64_t)b * p.a.G + g) * DV;
-    float vv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) vv[u] = lane + 64 * u < DV ? vn[lane + 64 * u] : 0.f;
-    float kk = 0.f;
-    if (lane < DR) {
-      const float* kn = static_cast<const float*>(p.a.kr_new) + (int64_t)b * DR;
-      double y0, y1;
-      const int pi = lane / 2;
-      rotate_pair(kn[2 * pi], kn[2 * pi + 1], (double)(L - 1) * p.inv_freq[pi], y0, y1);
-      kk = (float)((lane & 1) ? y1 : y0);
-    }
-    // the append of row L-1 (this wave is its only reader in this launch)
-    float* vcache = static_cast<float*>(p.a.v) + ((int64_t)b * p.a.G + g) * p.a.t_max * DV;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (lane + 64 * u < DV) vcache[tiled_off<float>(L - 1, lane + 64 * u, DV)] = vv[u];
-    if (g == 0 && lane < DR)
-      (static_cast<float*>(p.a.kr) + (int64_t)b * p.a.t_max * DR)[tiled_off<float>(L - 1, lane, DR)] = kk;
-#pragma unroll
-    for (int h = 0; h < kF32MaxHpg; ++h) {
-      if (h < hpg) {
-        float part = lane < DR ? qr[h][lane] * kk : 0.f;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (lane + 64 * u < DV) part = fmaf(qs[h][lane + 64 * u], vv[u], part);
-        const float x = wave_sum(part);
-        const float m_new = fmaxf(m_run[h], x);
-        const float alpha = __builtin_amdgcn_exp2f(m_run[h] - m_new);
-        const float pr = __builtin_amdgcn_exp2f(x - m_new);
-        l_run[h] = l_run[h] * alpha + pr;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[h][u] = acc[h][u] * alpha + pr * vv[u];
-        m_run[h] = m_new;
+    float* vcache = static_cast<float*>(a.v) + ((int64_t)b * a.G + g) * a.t_max * DV;
+    if (tid < 4 * NC) *(reinterpret_cast<f32x4*>(prow) + tid) = pend_piece;   // zeros past d_v
+    if (tid < DV / 4) *reinterpret_cast<f32x4*>(vcache + tiled_off<float>(L - 1, 4 * tid, DV)) = pend_piece;
+    if (tid < 8 * NRC) {
+      float y0f = 0.f, y1f = 0.f;
+      if (tid < DR / 2) {
+        double y0, y1;
+        rotate_pair(pk0, pk1, (double)(L - 1) * kfreq, y0, y1);
+        y0f = (float)y0;
+        y1f = (float)y1;
+        if (g == 0) {
+          float* kcache = static_cast<float*>(a.kr) + (int64_t)b * a.t_max * DR + tiled_off<float>(L - 1, 2 * tid, DR);
+          kcache[0] = y0f;
+          kcache[1] = y1f;
+        }
       }
+      prow[16 * NC + 2 * tid] = y0f;
+      prow[16 * NC + 2 * tid + 1] = y1f;
     }
   }
+  if (has_pair) {
+    double y0, y1;
+    rotate_pair(rq0, rq1, (double)(L > 0 ? L - 1 : 0) * qfreq, y0, y1);
+    qrs[pair_h * QRP + 2 * pair_i] = (float)(y0 * (double)a.scale_log2);
+    qrs[pair_h * QRP + 2 * pair_i + 1] = (float)(y1 * (double)a.scale_log2);
+  }
+  __syncthreads();
 
+  // ---- the query as B operands: lane (n, qd) holds entries 16 c + 4 qd .. + 3 of head n
+  f32x4 bq[NC], bk[NRC];
+  const bool active = n < hpg;
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int h = 0; h < kF32MaxHpg; ++h) {
-    if (h < hpg) {
-      if (lane == 0) {
-        red_ml[w][h][0] = m_run[h];
-        red_ml[w][h][1] = l_run[h];
-      }
+  for (int c = 0; c < NC; ++c) {
+    const int col = 16 * c + 4 * qd;
+    bq[c] = zero4;
+    if (active && col < DV)
+      bq[c] = fused ? *reinterpret_cast<const f32x4*>(qs + n * PITCH + col)
+                    : *reinterpret_cast<const f32x4*>(a.q_abs + ((int64_t)b * a.H + h0 + n) * DV + col) * a.scale_log2;
+  }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = lane + 64 * u;
-        if (i < DV) red_o[w][h][i] = acc[h][u];
-      }
+  for (int c = 0; c < NRC; ++c) {
+    const int col = 16 * c + 4 * qd;
+    bk[c] = zero4;
+    if (active && col < DR)
+      bk[c] = fused ? *reinterpret_cast<const f32x4*>(qrs + n * QRP + col)
+                    : *reinterpret_cast<const f32x4*>(a.q_rot + ((int64_t)b * a.H + h0 + n) * DR + col) * a.scale_log2;
+  }
+  __syncthreads();                             // the queries' LDS is the waves' transposition tiles from here on
+
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x4 acc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = zero4;
+  float* const tr = lds + w * 16 * PITCH;
+
+  auto compute_tile = [&](TileF& t, int row0, int row_end) __attribute__((always_inline)) {
+    const bool tail = row0 + kF32TileRows > row_end;
+    if (tail) {                                // rows past the end may hold anything
+      const bool dead = row0 + n >= row_end;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) t.v[c] = dead ? zero4 : t.v[c];
+#pragma unroll
+      for (int c = 0; c < NRC; ++c) t.k[c] = dead ? zero4 : t.k[c];
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4*>(tr + n * PITCH + 16 * c + 4 * qd) = t.v[c];
+    f32x4 sc[2] = {zero4, zero4};
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sc[e & 1] = mfma_f32(t.v[c][e], bq[c][e], sc[e & 1]);
+#pragma unroll
+    for (int c = 0; c < NRC; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sc[e & 1] = mfma_f32(t.k[c][e], bk[c][e], sc[e & 1]);
+    float x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      x[j] = sc[0][j] + sc[1][j];
+      if (tail && row0 + 4 * qd + j >= row_end) x[j] = -INFINITY;
+    }
+    const float mt = max_over_rows(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+    const float m_new = fmaxf(m_run, mt);
+    if (__ballot(m_new > m_run) != 0) {        // rescale only when a max grew
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      l_run *= alpha;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c] *= alpha;
+      m_run = m_new;
+    }
+    float pr[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      pr[j] = __builtin_amdgcn_exp2f(x[j] - m_run);
+      l_run += pr[j];
+    }
+    // the tile's rows, written above by the other lanes of this wave
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[c] = mfma_f32(tr[(4 * qd + j) * PITCH + 16 * c + n], pr[j], acc[c]);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();           // the next tile's rows are written after these reads
+  };
+
+  for (int jt = 0; jt < my_tiles; jt += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      const int j = jt + d;
+      if (j >= my_tiles) break;
+      load_tile(buf[(d + DEPTH - 1) % DEPTH], tile_row(j + DEPTH - 1));
+      __builtin_amdgcn_sched_barrier(0);
+      compute_tile(buf[d], tile_row(j), r1);
+    }
+  }
+  if (pending && w == 0) {                     // the current token's row, as a one-row tile
+    TileF t;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) t.v[c] = n == 0 ? *reinterpret_cast<const f32x4*>(prow + 16 * c + 4 * qd) : zero4;
+#pragma unroll
+    for (int c = 0; c < NRC; ++c)
+      t.k[c] = n == 0 ? *reinterpret_cast<const f32x4*>(prow + 16 * NC + 16 * c + 4 * qd) : zero4;
+    compute_tile(t, L - 1, L);
+  }
+
+  // ---- merge the waves and write this split's partial
+  l_run = sum_over_rows(l_run);
+  __syncthreads();                             // the transposition tiles are the records below
+  if (active) {
+    float* rec = lds + (w * kF32MaxHpg + n) * PITCH;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4*>(rec + 16 * c + 4 * qd) = acc[c];
+    if (qd == 0) {
+      rec[16 * NC] = m_run;
+      rec[16 * NC + 1] = l_run;
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < hpg * DV; idx += kThreads) {
+  for (int idx = tid; idx < hpg * DV; idx += NT) {
     const int hl = idx / DV, i = idx % DV;
     float mx = -INFINITY;
-    for (int ww = 0; ww < kWaves; ++ww) mx = fmaxf(mx, red_ml[ww][hl][0]);
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) mx = fmaxf(mx, lds[(ww * kF32MaxHpg + hl) * PITCH + 16 * NC]);
     float o = 0.f, lsum = 0.f;
     if (mx != -INFINITY) {
-      for (int ww = 0; ww < kWaves; ++ww) {
-        const float mw = red_ml[ww][hl][0];
-        const float sc = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - mx);
-        lsum += red_ml[ww][hl][1] * sc;
-        o += red_o[ww][hl][i] * sc;
+#pragma unroll
+      for (int ww = 0; ww < NW; ++ww) {
+        const float* rec = lds + (ww * kF32MaxHpg + hl) * PITCH;
+        const float sc = rec[16 * NC] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(rec[16 * NC] - mx);
+        lsum += rec[16 * NC + 1] * sc;
+        o += rec[i] * sc;
       }
       o /= lsum;
     }
-    const int64_t prow = ((int64_t)b * p.a.H + h0 + hl) * p.a.S + s;
-    p.a.o_part[prow * DV + i] = o;
-    if (i == 0) p.a.lse_part[prow] = mx == -INFINITY ? -INFINITY : (mx + log2f(lsum)) * kLn2;
+    const int64_t row = ((int64_t)b * a.H + h0 + hl) * a.S + s;
+    a.o_part[row * DV + i] = o;
+    if (i == 0) a.lse_part[row] = mx == -INFINITY ? -INFINITY : (mx + log2f(lsum)) * kLn2;
   }
 }
 
@@ -1314,6 +1446,27 @@ bool decode_kr_stream(const gva_dims* d) {
   return (long long)d->batch * d->n_groups >= device_cu_count();
 }
 
+template <int NC, int NW>
+DecodeFn pick_f32_nrc(int d_r) {
+  return d_r <= 16 ? decode_f32_kernel<NC, 1, NW> : (d_r <= 32 ? decode_f32_kernel<NC, 2, NW> : decode_f32_kernel<NC, 4, NW>);
+}
+
+// Waves per fp32 workgroup: eight while every CU has at most one workgroup
+// (us per step, eight against four waves: B1 T2000 H8 G2 d 128 18.1 and 20.0;
+// B32 T4096 H32 G8 d 128, 256 workgroups, 104 and 113; B16 T2000 H64 G8 45 and
+// 54; the longest chains, B2 T8000 H8 G8 at 16 splits, lose 3%), four past
+// that (B64 T1024 H16 G4, two per CU: 26.3 and 23.0).  Above d_v = 128 eight
+// waves would not have the registers.
+int f32_waves(const gva_dims* d, long long grid) {
+  return d->d_v <= 128 && grid <= device_cu_count() ? 8 : kWaves;
+}
+
+DecodeFn pick_f32_decode(int d_v, int d_r, int nw) {
+  if (d_v <= 64) return nw == kWaves ? pick_f32_nrc<4, kWaves>(d_r) : pick_f32_nrc<4, 8>(d_r);
+  if (d_v <= 128) return nw == kWaves ? pick_f32_nrc<8, kWaves>(d_r) : pick_f32_nrc<8, 8>(d_r);
+  return pick_f32_nrc<16, kWaves>(d_r);
+}
+
 // With launch = false every argument is checked and nothing is enqueued.
 int absorb_impl(const gva_dims* dims, int n_per_seq, const void* q, const void* m, const int32_t* lens,
                 float* q_abs, float* q_rot, void* stream, bool launch = true) {
@@ -1496,7 +1649,8 @@ int decode_attention_impl(const gva_dims* dims, const gva_paging* paging, const 
     if (dims->d_v > kF32MaxDv || dims->d_c > 512 || dims->d_r > kF32MaxDr || hpg > kF32MaxHpg)
       return GVA_ERR_UNSUPPORTED;
     if (!launch) return GVA_OK;
-    hipLaunchKernelGGL(decode_f32_kernel, dim3((unsigned)n_items), dim3(kThreads), 0, s, p);
+    const int nw = f32_waves(dims, n_items);
+    hipLaunchKernelGGL(pick_f32_decode(dims->d_v, dims->d_r, nw), dim3((unsigned)n_items), dim3(64 * nw), 0, s, p);
   }
   return launch_status();
 }

@@ -156,6 +156,49 @@ def test_shape_sweep_f32(H, G, dv, dc, dr):
         _check(w, o, lse, o_ref, lse_ref, f"f32/{H}/{G}/{dv}/{dc}/{dr}/S{S}")
 
 
+# fp32 storage works in 16-column chunks and 16-row tiles, with four or eight
+# waves: (B, H/G, G, d_v, d_c, d_r, T), widths on both sides of a chunk and of
+# the two and three instances, every number of positional chunks, and the last
+# case more workgroups than CUs (four waves).
+F32_EDGES = [
+    (3, 3, 2, 20, 5, 4, 64),
+    (3, 5, 1, 68, 70, 12, 176),
+    (3, 7, 2, 132, 128, 36, 96),
+    (2, 8, 1, 252, 33, 64, 80),
+    (3, 4, 2, 128, 100, 0, 304),
+    (100, 2, 3, 64, 64, 16, 32),
+]
+
+
+@pytest.mark.parametrize("B,hpg,G,dv,dc,dr,T", F32_EDGES)
+def test_f32_chunk_and_tile_edges(B, hpg, G, dv, dc, dr, T):
+    # one whole step (the current row appended) against the oracle, NaN in
+    # the cache's copy of that row and behind every length
+    w = gva_inputs.Workload("f32_edges", B, T, hpg * G, G, dv, dc, dr, dtype="f32")
+    lens = torch.tensor([(T, T - 15, 17, 16, 1, T - 1)[b % 6] for b in range(B)], dtype=torch.int32)
+    inp = gva_inputs.make_inputs(w, 67, lens=lens)
+    seq, pos = torch.arange(B, dtype=torch.int32), (lens - 1).to(torch.int32)
+    v_ref, k_ref = inp["v"].clone(), inp["kr"].clone()
+    oracle.append(v_ref, k_ref, inp["v_new"], inp["kr_new"], seq, pos, w.rope_base)
+    o_ref, lse_ref = oracle.decode(inp["q"], inp["m"], v_ref, k_ref, lens, rope_base=w.rope_base)
+    for b in range(B):
+        inp["v"][b, :, int(pos[b]):] = float("nan")
+        inp["kr"][b, int(pos[b]):] = float("nan")
+    d = dims_of(w)
+    for S, fused in ((1, True), (3, True), (2, False)):
+        label = f"f32 edges B{B} hpg{hpg} G{G} d{dv}/{dc}/{dr} T{T} S{S} fused={fused}"
+        note(label)
+        dev = upload(inp)
+        o, lse = gva.decode(d, dev["q"], dev["m"], dev["v"], dev["kr"], dev["lens"], S, fused=fused,
+                            v_new=dev["v_new"], kr_new=dev["kr_new"] if dr else None)
+        torch.cuda.synchronize()
+        _check(w, o.cpu(), lse.cpu(), o_ref, lse_ref, label)
+        for b in range(B):                     # the stored row, bit for bit
+            L = int(lens[b])
+            assert torch.equal(gva.untiled(dev["v"].cpu())[b, :, L - 1], v_ref[b, :, L - 1])
+            assert torch.equal(gva.untiled(dev["kr"].cpu())[b, L - 1], k_ref[b, L - 1]) or dr == 0
+
+
 # -------------------------------------------------------------- edge cases
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_ragged_and_degenerate_lengths(dtype):
