@@ -338,6 +338,30 @@ def test_append_matches_oracle_bitwise(dtype):
     assert torch.equal(gva.untiled(kd.cpu()).view(itype), k_ref.view(itype))
 
 
+@pytest.mark.parametrize("G,dv,dr,n,dtype", [(1, 24, 0, 1, "bf16"), (5, 24, 24, 17, "bf16"), (9, 200, 8, 48, "bf16"),
+                                             (2, 128, 64, 33, "f32"), (6, 12, 4, 16, "f32")])
+def test_append_prompt_rows_edges(G, dv, dr, n, dtype):
+    # consecutive rows (a prompt's) across layout tiles, in groups of sixteen
+    # with a remainder, group counts off the four waves, rows of fewer and of
+    # more 16-byte pieces than one pass moves
+    w = gva_inputs.Workload("append", 2, 64, 4 * G, G, dv, 64, dr, dtype=dtype)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(73)
+    v0, k0 = torch.randn(2, G, 64, dv, generator=g).to(tdt), torch.randn(2, 64, dr, generator=g).to(tdt)
+    v_new, k_new = torch.randn(n, G, dv, generator=g).to(tdt), torch.randn(n, dr, generator=g).to(tdt)
+    seq = torch.ones(n, dtype=torch.int32)
+    pos = torch.arange(7, 7 + n, dtype=torch.int32)
+    seq[n // 2] = 5                            # skipped
+    v_ref, k_ref = v0.clone(), k0.clone()
+    oracle.append(v_ref, k_ref, v_new, k_new, seq, pos, w.rope_base)
+    vd, kd = gva.tiled(v0).cuda(), gva.tiled(k0).cuda()
+    note(f"append prompt rows G{G} d{dv}/{dr} n{n} {dtype}")
+    gva.gva_append_kv(dims_of(w), vd, kd, v_new.cuda(), k_new.cuda(), seq.cuda(), pos.cuda())
+    torch.cuda.synchronize()
+    assert torch.equal(gva.untiled(vd.cpu()), v_ref)
+    assert torch.equal(gva.untiled(kd.cpu()), k_ref) or dr == 0
+
+
 def test_combine_matches_oracle():
     B, H, S, dv = 3, 4, 9, 128
     g = torch.Generator().manual_seed(37)
