@@ -953,6 +953,32 @@ def test_combine_never_reads_empty_partials():
     assert lse_err(lse.cpu(), lse_ref) <= 1e-5
 
 
+@pytest.mark.parametrize("S,dv", [(1, 64), (2, 65), (8, 128), (9, 32), (16, 128), (16, 200), (17, 64)])
+def test_combine_few_splits_edges(S, dv):
+    # both sides of the partials requested ahead (eight) and of the splits one
+    # 16-lane row holds (sixteen); empty splits, whose partials hold NaN, at
+    # the front, in the middle and everywhere
+    g = torch.Generator().manual_seed(71)
+    B, H = 3, 5
+    o_part = torch.randn(B, H, S, dv, generator=g)
+    lse_part = torch.randn(B, H, S, generator=g) * 4
+    lse_part[0, 1, 0] = -math.inf
+    lse_part[1, 2, S // 2:] = -math.inf
+    lse_part[2, :, 1::2] = -math.inf
+    lse_part[2, 4] = -math.inf
+    o_ref, lse_ref = oracle.combine(o_part, lse_part)
+    o_part[torch.isneginf(lse_part)] = float("nan")
+    w = gva_inputs.Workload("combine", B, 64, H, 1, dv, 64, 0)
+    o = torch.full((B, H, dv), float("nan"), device="cuda")
+    lse = torch.full((B, H), float("nan"), device="cuda")
+    note(f"combine S={S} dv={dv}")
+    gva.gva_combine(dims_of(w), o_part.cuda(), lse_part.cuda(), S, o, lse)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.cpu()).all()
+    assert max_abs(o.cpu(), o_ref) <= 1e-5
+    assert lse_err(lse.cpu(), lse_ref) <= 1e-5
+
+
 # ------------------------------------------------- HIP graph capture of steps
 @pytest.mark.parametrize("S,fused", [(1, True), (3, False)])
 def test_graph_capture_of_layer_steps(S, fused):
