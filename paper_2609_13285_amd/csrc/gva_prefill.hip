@@ -419,27 +419,32 @@ constexpr int kPrefillCols = 128;             // (position, head) columns per wo
 //    three buffers), so no wave holds a tile in registers and each row is
 //    requested once per workgroup;
 //  - every wave reads them as A operands for its scores S^T = [V | kr] q^T,
-//    the query's bf16 high and low parts both in registers as B operands.
-//    The accumulator starts at minus the column's running maximum, so the
-//    products arrive as the softmax's exponents;
+//    the query's bf16 high and low parts both in registers as B operands;
 //  - wave w turns value block w (at d_v = 64, waves 0 and 1) into V^T in fp16
 //    with identity products and puts it in LDS for all four (two buffers), in
 //    the row order in which the score registers lie, so a wave's softmax
 //    weights are the B operand of its P.V as they are;
-//  - P.V runs one tile behind the scores, its products between the softmax's
-//    exponentials.
+//  - the softmax and P.V run one tile behind the scores: the previous tile's
+//    exponentials stand between this tile's score products, this tile's maxima
+//    between the previous tile's P.V.  (Two or three vector instructions
+//    beside a 32x32x16 product are nearly free, a run of them between products
+//    costs its full time: softmax and P.V of one tile together, after its
+//    scores, took 80.9 us where this takes 76.5, four 2048-token prompts at
+//    H16 G4 d 64/16 with their append, and 200.6 against 196.7 for the
+//    baseline below.)
 // One barrier per tile.
 //
 // What bounds it: at d_v = 128 the matrix cores' power.  They are busy 63% of
 // the cycles, at which the clock settles at 1.9 GHz (a large bf16 library
 // product: 70% at 2.0 GHz; the kernel this replaced, every wave reading whole
 // tiles into registers and transposing in 16-wide products: 49% at 2.3 GHz).
-// At d_v = 64 the softmax, twice as much per product.  Measured, whole calls
-// from the raw queries against the separate absorption and the former
-// kernels: H32 G8 d 128/16, 8192 tokens 878 -> 748 us; H16 G4 d 64/16, four
-// 2048-token prompts 131 -> 75 us; the matched-GQA baseline at H32 G8 d 128,
-// 4096 tokens 310 -> 202 us.  Three waves per SIMD at d_v = 64 (168
-// registers) spill and lose (8192 tokens 240 -> 258 us).
+// At d_v = 64 the softmax, twice as much per product, and each workgroup's
+// start.  Measured, append and prompt from the raw queries against the
+// separate absorption and the former kernels: H32 G8 d 128/16, 8192 tokens
+// 899 -> 759 us; H16 G4 d 64/16, four 2048-token prompts 141 -> 76.5 us; the
+// matched-GQA baseline at H32 G8 d 128, 4096 tokens 310 -> 197 us.  With 168
+// registers for three waves per SIMD at d_v = 64, 8192 tokens took 258 us
+// against 240 (spills).
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
@@ -484,10 +489,10 @@ struct PrefillCfg {
   static constexpr int TILE_BYTES = V_BYTES * (GQA ? 2 : 1) + NRC * 1024;
   static constexpr int VT_BYTES = V_BYTES;
   static constexpr int GROUP_BYTES = 3 * TILE_BYTES + 2 * VT_BYTES;   // one set of four waves
-  // operands read from LDS ahead of their products: scores, and of the P.V's
-  // V^T before the softmax (fewer where four positional chunks hold the registers)
-  static constexpr int READ_AHEAD = DV >= 128 && NRC > 2 ? 3 : 5;
-  static constexpr int VT_AHEAD = DV >= 128 && NRC > 2 ? 1 : 4;
+  // operands read from LDS ahead of their products: of the scores, and of the
+  // P.V's V^T before it begins (fewer where the positional chunks hold the registers)
+  static constexpr int READ_AHEAD = DV >= 128 && NRC > 1 ? 3 : 4;
+  static constexpr int VT_AHEAD = DV >= 128 && NRC > 1 ? 2 : 4;
   static constexpr int COPIES = KB / 4 * (GQA ? 2 : 1) + (NRC > 0 ? 1 : 0);   // per wave and tile
   static constexpr int MERGE_BYTES = KS > 1 ? kWaves * 64 * (NIB * 16 + 2) * 4 : 0;
   static constexpr int LDS = KS * GROUP_BYTES > MERGE_BYTES ? KS * GROUP_BYTES : MERGE_BYTES;
@@ -669,13 +674,12 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
     esel[c] = as_bf16x8(u);
   }
 
-  f32x16 acc[NIB], negm;
+  f32x16 acc[NIB];
   float m_run = 0.f, l_run = 0.f;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) negm[r] = 0.f;
+  for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
-  for (int ib = 0; ib < NIB; ++ib) acc[ib] = negm;
-  f16x8 bp[2];
+    for (int r = 0; r < 16; ++r) acc[ib][r] = 0.f;
 
   const int v_off = (n >> 4) * (DV * 32) + h * 256 + (n & 15) * 16;   // this lane's piece of chunk 0
   const char* const vt_lane = grp_lds + 3 * Cfg::TILE_BYTES + lane * 16;
@@ -683,67 +687,69 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
     return *reinterpret_cast<const f16x8*>(vt_lane + vbuf * Cfg::VT_BYTES + k * 1024);
   };
 
-  // One tile; FIRST: the workgroup's first, which has no P.V before it and
-  // sets the running maxima.
-  auto step = [&](auto first_tag, int j, int buf) {
+  // element r of the softmax weights of scores sc
+  auto exps = [&](const f32x16& sc, float (&pr)[16], int r) {
+    pr[r] = __builtin_amdgcn_exp2f(sc[r] - m_run);
+    l_run += pr[r];
+  };
+  // One tile: scores sn of tile j, beside them the softmax weights of the
+  // tile before (scores sp), then that tile's P.V, beside it tile j's maxima.
+  // The orders are pinned (scheduling barriers): on these matrix cores a few
+  // vector instructions between two products are nearly free, a run of them
+  // is not.  FIRST: the workgroup's first tile, with none before it.
+  auto step = [&](auto first_tag, int j, int buf, const f32x16& sp, f32x16& sn) __attribute__((always_inline)) {
     constexpr bool FIRST = decltype(first_tag)::value;
     const int row0 = tile_row(j);
     copy_tile(tile_row(j + 2), buf == 0 ? 2 : buf - 1);
     const char* vtile = grp_lds + buf * Cfg::TILE_BYTES;
     const char* ktile = vtile + Cfg::V_BYTES;
-    __builtin_amdgcn_s_setprio(0);
-    // scores, as exponents relative to the running maximum
-    f32x16 s = negm;
-    bf16x8 a[NCH], ar[NRC > 0 ? NRC : 1];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) a[c] = *reinterpret_cast<const bf16x8*>((GQA ? ktile : vtile) + v_off + c * 512);
-#pragma unroll
-    for (int rc = 0; rc < NRC; ++rc) ar[rc] = *reinterpret_cast<const bf16x8*>(ktile + k_off[rc]);
-    const int tw = w < NIB ? w : 0;
-    bf16x8 at[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) at[c] = *reinterpret_cast<const bf16x8*>(vtile + v_off + (2 * tw + c) * 512);
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      s = mfma32(a[c], qh[c], s);
-      s = mfma32(a[c], ql[c], s);
-    }
-#pragma unroll
-    for (int rc = 0; rc < NRC; ++rc) {
-      s = mfma32(ar[rc], rh[rc], s);
-      s = mfma32(ar[rc], rl[rc], s);
-    }
-    // this wave's block of V^T (at d_v = 64 waves 2 and 3 repeat block 0 and drop it)
+    const int tw = w < NIB ? w : 0;            // this wave's block of V^T (waves past it repeat block 0 and drop it)
+    // operand k of the tile: the score chunks, the positional ones, the V^T block's
+    constexpr int NA = NCH + NRC, NOP = NA + 2;
+    auto operand = [&](int k) {
+      if (k < NCH) return *reinterpret_cast<const bf16x8*>((GQA ? ktile : vtile) + v_off + k * 512);
+      if (k < NA) return *reinterpret_cast<const bf16x8*>(ktile + k_off[k < NA && k >= NCH ? k - NCH : 0]);
+      return *reinterpret_cast<const bf16x8*>(vtile + v_off + (2 * tw + k - NA) * 512);
+    };
+    bf16x8 a[NOP];
+    f16x8 av[2 * NIB];
+    float pr[16];
+    f16x8 bn[2];
     f32x16 t;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) t[r] = 0.f;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) t = mfma32(at[c], esel[c], t);
-    // the previous tile's V^T
-    f16x8 av[2 * NIB];
-    if constexpr (!FIRST) {
-#pragma unroll
-      for (int k = 0; k < VA; ++k) av[k] = vt_piece((j & 1) ^ 1, k);
-    }
-    // LDS reads run RA operands ahead of the products that use them
-    __builtin_amdgcn_sched_group_barrier(0x100, RA, 0);
-#pragma unroll
-    for (int k = 0; k < NCH + NRC + 2 - RA; ++k) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-#pragma unroll
-    for (int k = 0; k < VA; ++k) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 64, 0);
+    for (int k = 0; k < RA; ++k) a[k] = operand(k);
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(1);             // the softmax goes before the other waves' products
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sn[r] = t[r] = 0.f;
+    constexpr int NM = 2 * NA + 2;             // products of this phase
+    __builtin_amdgcn_s_setprio(1);             // ahead of the other wave's P.V, which has less to interleave
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      const int k = i < 2 * NA ? i / 2 : i - NA;
+      if (k < NCH) sn = mfma32(a[k], (i & 1) ? ql[k < NCH ? k : 0] : qh[k < NCH ? k : 0], sn);
+      else if (k < NA) sn = mfma32(a[k], (i & 1) ? rl[k < NA && k >= NCH ? k - NCH : 0] : rh[k < NA && k >= NCH ? k - NCH : 0], sn);
+      else t = mfma32(a[k], esel[k - NA], t);
+      if ((i & 1) == 1 || i >= 2 * NA) {
+        if (k + RA < NOP) a[k + RA] = operand(k + RA);
+        else if (!FIRST && k + RA - NOP < VA) av[k + RA - NOP] = vt_piece((j & 1) ^ 1, k + RA - NOP);
+      }
+      if constexpr (!FIRST) {
+        // sixteen exponentials over the phase's products
+#pragma unroll
+        for (int r = i * 16 / NM; r < (i + 1) * 16 / NM; ++r) {
+          exps(sp, pr, r);
+          if (r == 7) bn[0] = to_f16x8(pr);
+          if (r == 15) bn[1] = to_f16x8(pr + 8);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (!FIRST) asm volatile("" ::"v"(bn[0]), "v"(bn[1]), "v"(l_run));   // formed here, beside the products
+    __builtin_amdgcn_sched_barrier(0);
     if (row0 + kTileRows - 1 > p_first) {      // some column may not see every row
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        if (row0 + score_row(r, h) > pos) s[r] = -INFINITY;
+        if (row0 + score_row(r, h) > pos) sn[r] = -INFINITY;
     }
     // rows past the block's keys may hold anything (a wave whose columns all
     // lie past the prompt's last row masks nothing, but its V^T block counts)
@@ -752,86 +758,77 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
       for (int r = 0; r < 16; ++r)
         if (row0 + score_row(r, h) >= kend) t[r] = 0.f;
     }
-    float mt = s[0];
+    __builtin_amdgcn_s_setprio(0);
+    float mt = -INFINITY;
+    char* vt = grp_lds + 3 * Cfg::TILE_BYTES + (j & 1) * Cfg::VT_BYTES + lane * 16;
 #pragma unroll
-    for (int r = 1; r < 16; ++r) mt = fmaxf(mt, s[r]);
+    for (int k = 0; k < 2 * NIB; ++k) {
+      if constexpr (!FIRST) {
+        acc[k >> 1] = mfma32(av[k], bn[k & 1], acc[k >> 1]);
+        if (k + VA < 2 * NIB) av[k + VA] = vt_piece((j & 1) ^ 1, k + VA);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int r = k * (8 / NIB); r < (k + 1) * (8 / NIB); ++r) mt = fmaxf(mt, sn[r]);
+      if (k == 0 || k == NIB) {
+        float x8[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x8[e] = t[8 * (k / NIB) + e];
+        const f16x8 tv = to_f16x8(x8);         // bf16 values: exact in fp16 at these magnitudes
+        if (w < NIB) *reinterpret_cast<f16x8*>(vt + (2 * w + k / NIB) * 1024) = tv;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
     {
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
       mt = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     }
     // The maximum is the first tile's, and moves when a column's tile
-    // maximum exceeds it by more than kLazyMax (log2 units).  The
-    // accumulators are rescaled after the P.V below, whose weights are
-    // relative to the old maximum.
-    const bool grow = FIRST || __ballot(mt > kLazyMax) != 0;
-    float alpha = 1.f;
-    if (grow) {
-      float m_new = m_run + (FIRST ? mt : fmaxf(mt, 0.f));
+    // maximum exceeds it by more than kLazyMax (log2 units).
+    if (FIRST || __ballot(mt > m_run + kLazyMax) != 0) {
+      float m_new = FIRST ? mt : fmaxf(mt, m_run);
       if (mt == -INFINITY) m_new = m_run;      // no row of the tile is the column's
-      const float d = m_new - m_run;
-      alpha = __builtin_amdgcn_exp2f(-d);
-      m_run = m_new;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        s[r] -= d;
-        negm[r] = -m_new;
-      }
-      if constexpr (!FIRST) l_run *= alpha;
-    }
-    float pr[16];
-    f16x8 bn[2], tv[2];
-    // P.V of the previous tile with this tile's exponentials between its
-    // products, in the order written (scheduling barriers)
-#pragma unroll
-    for (int k = 0; k < 2 * NIB; ++k) {
       if constexpr (!FIRST) {
-        acc[k >> 1] = mfma32(av[k], bp[k & 1], acc[k >> 1]);
-        if (k + VA < 2 * NIB) av[k + VA] = vt_piece((j & 1) ^ 1, k + VA);
-        __builtin_amdgcn_sched_barrier(0);
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        l_run *= alpha;
+#pragma unroll
+        for (int ib = 0; ib < NIB; ++ib) acc[ib] *= alpha;
       }
-#pragma unroll
-      for (int r = k * (8 / NIB); r < (k + 1) * (8 / NIB); ++r) {
-        pr[r] = __builtin_amdgcn_exp2f(s[r]);
-        l_run += pr[r];
-      }
-      if (k + 1 == NIB || k + 1 == 2 * NIB) bn[k / NIB] = to_f16x8(pr + 8 * (k / NIB));
-      if (k == 0 || k == NIB) {
-        float x8[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x8[e] = t[8 * (k / NIB) + e];
-        tv[k / NIB] = to_f16x8(x8);            // bf16 values: exact in fp16 at these magnitudes
-      }
-      __builtin_amdgcn_sched_barrier(0);
+      m_run = m_new;
     }
-    asm volatile("" ::"v"(bn[0]), "v"(bn[1]), "v"(l_run));   // formed here, beside the products, not after them
-    __builtin_amdgcn_sched_barrier(0);
-    if (w < NIB) {
-      char* vt = grp_lds + 3 * Cfg::TILE_BYTES + (j & 1) * Cfg::VT_BYTES + lane * 16;
-#pragma unroll
-      for (int c = 0; c < 2; ++c) *reinterpret_cast<f16x8*>(vt + (2 * w + c) * 1024) = tv[c];
-    }
-    if (!FIRST && grow) {
-#pragma unroll
-      for (int ib = 0; ib < NIB; ++ib) acc[ib] *= alpha;
-    }
-    bp[0] = bn[0];
-    bp[1] = bn[1];
     wait_copies<Cfg::COPIES>();                // the next tile has landed (the one after it may be in flight)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's V^T block is in LDS
     __builtin_amdgcn_s_barrier();
+  };
+  auto last = [&](const f32x16& sp) {          // the last tile's weights and P.V
+    float pr[16];
+    f16x8 bn[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) exps(sp, pr, r);
+    bn[0] = to_f16x8(pr);
+    bn[1] = to_f16x8(pr + 8);
+#pragma unroll
+    for (int k = 0; k < 2 * NIB; ++k) acc[k >> 1] = mfma32(vt_piece((nit - 1) & 1, k), bn[k & 1], acc[k >> 1]);
   };
 
   wait_copies<Cfg::COPIES>();
   __builtin_amdgcn_s_barrier();
   if (nit > 0) {
-    step(std::true_type{}, 0, 0);
-    int buf = 1;
-    for (int j = 1; j < nit; ++j) {
-      step(std::false_type{}, j, buf);
+    f32x16 s0, s1;                             // the scores of even and odd tiles
+    step(std::true_type{}, 0, 0, s0, s0);
+    int buf = 1, j = 1;
+    for (; j + 1 < nit; j += 2) {
+      step(std::false_type{}, j, buf, s0, s1);
+      buf = buf == 2 ? 0 : buf + 1;
+      step(std::false_type{}, j + 1, buf, s1, s0);
       buf = buf == 2 ? 0 : buf + 1;
     }
-#pragma unroll
-    for (int k = 0; k < 2 * NIB; ++k) acc[k >> 1] = mfma32(vt_piece((nit - 1) & 1, k), bp[k & 1], acc[k >> 1]);
+    if (j < nit) {
+      step(std::false_type{}, j, buf, s0, s1);
+      last(s1);
+    } else {
+      last(s0);
+    }
   }
 
   // ---- merge the two sets of waves, normalise, write
