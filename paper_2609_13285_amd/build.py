@@ -24,6 +24,8 @@ LIB = os.path.join(HERE, "libgva.so")
 ARCH = "gfx950"
 FLAGS = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # leading scalar kernel arguments in registers before a wave starts
+         "-mllvm", "-amdgpu-kernarg-preload-count=14",
          "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 

@@ -353,11 +353,11 @@ struct DecodeCfg {
 // KR_STREAM loads the positional-key tiles with the non-temporal policy too
 // (decode_kr_stream decides).
 template <int HPG, int DV, int NRC, bool GQA, bool FUSED, bool PAGED, bool KR_STREAM = false, int NW = kWaves>
-__global__ void __launch_bounds__(64 * NW, NW == kWaves ? 2 : 1) decode_bf16_kernel(DecodeParams p) {
+__global__ void __launch_bounds__(64 * NW, NW == kWaves ? 2 : 1)
+    decode_bf16_kernel(GVA_DECODE_HEAD_ARGS, DecodeParams p) {
   static_assert(!(GQA && FUSED), "the GQA baseline takes the raw query");
   static_assert(!(GQA && PAGED), "the GQA baseline reads contiguous caches");
-  const DecodeArgs a = p.a;
-  request_args<FUSED || GQA>(a);
+  const DecodeArgs a = decode_args<FUSED || GQA>(GVA_DECODE_HEAD_NAMES, p);
   using Cfg = DecodeCfg<HPG, DV, NRC, NW, GQA>;
   constexpr int NT = 64 * NW;                  // threads per workgroup
   using TileT = Tile<DV, NRC, GQA>;
@@ -478,6 +478,7 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves ? 2 : 1) decode_bf16_ker
     if (w < HPG) load_round(w, 0);
   }
   __builtin_amdgcn_sched_barrier(0);
+  request_args(a);
   if (!settle_rows()) {
     write_empty();
     return;
@@ -947,15 +948,16 @@ struct F32Cfg {
 };
 
 template <int NC, int NRC, int NW>
-__global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1) decode_f32_kernel(DecodeParams p) {
+__global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1)
+    decode_f32_kernel(GVA_DECODE_HEAD_ARGS, DecodeParams p) {
   using Cfg = F32Cfg<NC, NRC, NW>;
   constexpr int NT = 64 * NW, DEPTH = Cfg::DEPTH, AR = Cfg::AR, PITCH = Cfg::PITCH, QRP = Cfg::QR_PITCH;
-  const DecodeArgs a = p.a;
-  const bool fused = a.q != nullptr;
-  asm volatile("" ::"s"(a.B), "s"(a.H), "s"(a.G), "s"(a.S), "s"(a.t_max), "s"(a.split_rows), "s"(a.d_r), "s"(a.d_c),
-               "s"(a.d_v), "s"(a.lens), "s"(a.v_new), "s"(a.kr_new), "s"(a.q), "s"(a.m), "s"(a.q_abs), "s"(a.q_rot),
-               "s"(gridDim.x)
-               : "memory");                    // one round trip for the arguments, as request_args
+  const bool fused = (head_dims >> 26 & 1) != 0;
+  DecodeArgs a = decode_args<true>(GVA_DECODE_HEAD_NAMES, p);
+  if (!fused) {                                // the same two places carry the absorbed query
+    a.q_abs = static_cast<const float*>(a.q);
+    a.q_rot = static_cast<const float*>(a.m);
+  }
   __shared__ __attribute__((aligned(16))) float lds[Cfg::LDS_FLOATS];
   __shared__ __attribute__((aligned(16))) float prow[16 * NC + 16 * NRC];   // the current token's row
 
@@ -1027,6 +1029,7 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1) deco
   }
   if (w < njobs && nseg > 0) load_round(w, 0);
   __builtin_amdgcn_sched_barrier(0);
+  request_args(a);
 
   const int L = len_b < 0 ? 0 : (len_b > a.t_max ? a.t_max : len_b);
   int r0, r1;
@@ -1273,6 +1276,8 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1) deco
 // One wave per (b, h) row, lane = output element (up to 4 per lane).  A
 // single pass keeps a running log-sum-exp and rescales the running sum;
 // the split loads do not depend on each other, so they overlap.
+// (Scalar arguments, all of them in registers before a wave starts: see
+// GVA_DECODE_HEAD_ARGS.)
 constexpr int kCombineMaxDv = 256;
 constexpr long long kChunkItemsPerCu = 2;         // bounded chunks: chunks per CU
 constexpr long long kMinChunkBytes = 128 << 10;   // bounded chunks: value bytes per chunk
@@ -1280,18 +1285,19 @@ constexpr long long kMinSplitStream = 192 << 10;  // even splits: a stream's val
 constexpr long long kMinSplitBytes = 32 << 10;    // even splits: value bytes per split
 constexpr long long kMaxEvenSplits = 16;
 
-__global__ void __launch_bounds__(kThreads) combine_kernel(CombineParams p) {
+__global__ void __launch_bounds__(kThreads) combine_kernel(const float* o_part, const float* lse_part, float* o, float* lse,
+                                                          int32_t rows, int32_t S, int32_t d_v) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * kWaves + (threadIdx.x >> 6);
-  if (row >= p.rows) return;
-  const float* lp = p.lse_part + (int64_t)row * p.S;
-  const float* op = p.o_part + (int64_t)row * p.S * p.d_v;
+  if (row >= rows) return;
+  const float* lp = lse_part + (int64_t)row * S;
+  const float* op = o_part + (int64_t)row * S * d_v;
   // the row's split LSEs, up to 4 per lane (S <= 256), and their maximum
   float l[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int s = lane + 64 * k;
-    l[k] = s < p.S ? lp[s] : -INFINITY;
+    l[k] = s < S ? lp[s] : -INFINITY;
   }
   // The first kSpec splits' partials are requested with the LSEs, before it
   // is known which are empty (splits hold a sequence's rows from the front,
@@ -1305,7 +1311,7 @@ __global__ void __launch_bounds__(kThreads) combine_kernel(CombineParams p) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int i = lane + 64 * u;
-      v0[j][u] = (j < p.S && i < p.d_v) ? op[(int64_t)j * p.d_v + i] : 0.f;
+      v0[j][u] = (j < S && i < d_v) ? op[(int64_t)j * d_v + i] : 0.f;
     }
   float mx = -INFINITY;
 #pragma unroll
@@ -1323,7 +1329,7 @@ __global__ void __launch_bounds__(kThreads) combine_kernel(CombineParams p) {
     z = wave_sum(z);
 #pragma unroll
     for (int j = 0; j < kSpec; ++j) {
-      if (j >= p.S) break;
+      if (j >= S) break;
       const float wj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wk[0]), j));
       const bool live = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l[0]), j)) != -INFINITY;
 #pragma unroll
@@ -1332,7 +1338,7 @@ __global__ void __launch_bounds__(kThreads) combine_kernel(CombineParams p) {
     // the remaining splits with rows, 8 at a time so their loads overlap
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      if (64 * k >= p.S) break;
+      if (64 * k >= S) break;
       unsigned long long mask = __ballot(l[k] != -INFINITY);
       if (k == 0) mask &= ~((1ull << kSpec) - 1ull);
       while (mask != 0ull) {
@@ -1355,7 +1361,7 @@ __global__ void __launch_bounds__(kThreads) combine_kernel(CombineParams p) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int i = lane + 64 * u;
-            v[j][u] = (sel[j] >= 0 && i < p.d_v) ? op[(int64_t)sel[j] * p.d_v + i] : 0.f;
+            v[j][u] = (sel[j] >= 0 && i < d_v) ? op[(int64_t)sel[j] * d_v + i] : 0.f;
           }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -1368,9 +1374,9 @@ __global__ void __launch_bounds__(kThreads) combine_kernel(CombineParams p) {
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int i = lane + 64 * u;
-    if (i < p.d_v) p.o[(int64_t)row * p.d_v + i] = acc[u] * inv;
+    if (i < d_v) o[(int64_t)row * d_v + i] = acc[u] * inv;
   }
-  if (p.lse != nullptr && lane == 0) p.lse[row] = mx == -INFINITY ? -INFINITY : mx + logf(z);
+  if (lse != nullptr && lane == 0) lse[row] = mx == -INFINITY ? -INFINITY : mx + logf(z);
 }
 
 // At most kFewSplits splits: lanes n and n + 16 k hold split n's LSE, so the
@@ -1394,20 +1400,21 @@ __device__ __forceinline__ float max16(float x) {
 }
 
 template <int U>
-__global__ void __launch_bounds__(kThreads) combine_few_kernel(CombineParams p) {
+__global__ void __launch_bounds__(kThreads) combine_few_kernel(const float* o_part, const float* lse_part, float* o, float* lse,
+                                                          int32_t rows, int32_t S, int32_t d_v) {
   const int lane = threadIdx.x & 63, n = lane & 15;
   const int row = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
-  if (row >= p.rows) return;
-  const float* op = p.o_part + (int64_t)row * p.S * p.d_v;
+  if (row >= rows) return;
+  const float* op = o_part + (int64_t)row * S * d_v;
   constexpr int kSpec = 8;
-  const float l = n < p.S ? p.lse_part[(int64_t)row * p.S + n] : -INFINITY;
+  const float l = n < S ? lse_part[(int64_t)row * S + n] : -INFINITY;
   float v[kSpec][U];
 #pragma unroll
   for (int j = 0; j < kSpec; ++j)
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = lane + 64 * u;
-      v[j][u] = (j < p.S && i < p.d_v) ? op[(int64_t)j * p.d_v + i] : 0.f;
+      v[j][u] = (j < S && i < d_v) ? op[(int64_t)j * d_v + i] : 0.f;
     }
   const float mx = fmaxf(max16(l), -INFINITY);
   const bool any = mx != -INFINITY;
@@ -1430,7 +1437,7 @@ __global__ void __launch_bounds__(kThreads) combine_few_kernel(CombineParams p) 
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = lane + 64 * u;
-        x[j - kSpec][u] = i < p.d_v ? op[(int64_t)((live >> j & 1) ? j : 0) * p.d_v + i] : 0.f;
+        x[j - kSpec][u] = i < d_v ? op[(int64_t)((live >> j & 1) ? j : 0) * d_v + i] : 0.f;
       }
 #pragma unroll
     for (int j = 0; j < kSpec; ++j) add(j, v[j]);
@@ -1444,12 +1451,22 @@ __global__ void __launch_bounds__(kThreads) combine_few_kernel(CombineParams p) 
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int i = lane + 64 * u;
-    if (i < p.d_v) p.o[(int64_t)row * p.d_v + i] = acc[u] * inv;
+    if (i < d_v) o[(int64_t)row * d_v + i] = acc[u] * inv;
   }
-  if (p.lse != nullptr && lane == 0) p.lse[row] = mx == -INFINITY ? -INFINITY : mx + logf(z);
+  if (lse != nullptr && lane == 0) lse[row] = mx == -INFINITY ? -INFINITY : mx + logf(z);
 }
 
-using DecodeFn = void (*)(DecodeParams);
+using DecodeFn = void (*)(GVA_DECODE_HEAD_ARGS, DecodeParams);
+
+// Enqueues a decode launch; the leading arguments repeat those of p that the
+// kernel's first instructions need.
+void launch_decode(DecodeFn fn, long long grid, int threads, hipStream_t s, const DecodeParams& p, bool raw_query) {
+  const DecodeArgs& a = p.a;
+  const int dims = a.d_c | a.d_r << 10 | a.S << 17 | (raw_query ? 1 << 26 : 0) | (a.H / a.G) << 27;
+  hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(threads), 0, s, a.lens, raw_query ? a.q : a.q_abs,
+                     raw_query ? a.m : a.q_rot, a.v_new, a.kr_new, dims, a.B, a.G, a.split_rows, p);
+}
+
 
 template <int HPG, int DV, bool FUSED, bool PAGED>
 DecodeFn pick_nrc(int nrc, bool kr_stream) {
@@ -1759,14 +1776,14 @@ int decode_attention_impl(const gva_dims* dims, const gva_paging* paging, const 
     DecodeFn fn = pick_bf16_decode(hpg, dims->d_v, nrc, fused, paging != nullptr, decode_kr_stream(dims), nw);
     if (fn == nullptr) return GVA_ERR_UNSUPPORTED;
     if (!launch) return GVA_OK;
-    hipLaunchKernelGGL(fn, dim3((unsigned)n_items), dim3(64 * nw), 0, s, p);
+    launch_decode(fn, n_items, 64 * nw, s, p, fused);
   } else {
     if (paging != nullptr) return GVA_ERR_UNSUPPORTED;       // paged caches: bf16 only
     if (dims->d_v > kF32MaxDv || dims->d_c > 512 || dims->d_r > kF32MaxDr || hpg > kF32MaxHpg)
       return GVA_ERR_UNSUPPORTED;
     if (!launch) return GVA_OK;
     const int nw = f32_waves(dims, n_items);
-    hipLaunchKernelGGL(pick_f32_decode(dims->d_v, dims->d_r, nw), dim3((unsigned)n_items), dim3(64 * nw), 0, s, p);
+    launch_decode(pick_f32_decode(dims->d_v, dims->d_r, nw), n_items, 64 * nw, s, p, fused);
   }
   return launch_status();
 }
@@ -1781,20 +1798,14 @@ int combine_impl(const gva_dims* dims, const float* o_part, const float* lse_par
     return GVA_ERR_INVALID_ARG;
   if (dims->d_v > kCombineMaxDv) return GVA_ERR_UNSUPPORTED;
   if (!launch) return GVA_OK;
-  CombineParams p{};
-  p.o_part = o_part;
-  p.lse_part = lse_part;
-  p.o = o;
-  p.lse = lse;
-  p.rows = dims->batch * dims->n_heads;
-  p.S = num_splits;
-  p.d_v = dims->d_v;
-  const dim3 grid((p.rows + kWaves - 1) / kWaves);
+  const int rows = dims->batch * dims->n_heads;
+  const dim3 grid((rows + kWaves - 1) / kWaves);
   const auto fn = num_splits > kFewSplits ? combine_kernel
                   : dims->d_v <= 64       ? combine_few_kernel<1>
                   : dims->d_v <= 128      ? combine_few_kernel<2>
                                           : combine_few_kernel<4>;
-  hipLaunchKernelGGL(fn, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), p);
+  hipLaunchKernelGGL(fn, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), o_part, lse_part, o, lse, rows,
+                     num_splits, dims->d_v);
   return launch_status();
 }
 
@@ -2000,7 +2011,7 @@ int gva_gqa_decode_attention(const gva_dims* dims, const void* q, int32_t q_stri
   p.a.split_rows = split_rows;
   const double sc = dims->scale > 0.0 ? dims->scale : 1.0 / sqrt((double)dims->d_v);
   p.a.scale_log2 = (float)(sc * kLog2e);
-  hipLaunchKernelGGL(fn, dim3((unsigned)n_items), dim3(kThreads), 0, static_cast<hipStream_t>(stream), p);
+  launch_decode(fn, n_items, kThreads, static_cast<hipStream_t>(stream), p, true);
   return launch_status();
 }
 
