@@ -180,11 +180,12 @@ __device__ __forceinline__ int xcd_remap(int x, int n) {
 //    multiple of 8, split x of every sequence on XCD x, the same share of
 //    each sequence whatever the lengths; with S = 1, whole sequences that
 //    lie next to each other in memory.
-//  - Bounded chunks (see chunk_item): the (b, s) slots in the order
-//    chunks with rows, then empty slots, dealt round-robin over the XCDs
-//    (slot k to XCD k mod 8), so chunks of every length spread over all of
-//    them; the grid is B * S rounded up to 8, times G, and workgroups past
-//    B * S are padding and return false.
+//  - Bounded chunks (see chunk_item): the (b, s) slots in the order chunks
+//    with rows, then empty slots, dealt over the XCDs back and forth (slots
+//    0..7 to XCDs 0..7, 8..15 to 7..0, ...); the grid is B * S rounded up to
+//    8, times G, and workgroups past B * S are padding and return false.
+//    (Dealt in one direction only: B100 to 4096 rows, H16 G4 d 128, 33.4
+//    against 32.6 us.)
 // The arguments that a decode kernel's first instructions need come ahead of
 // the parameter block as 14 scalar registers: the build asks for kernel
 // arguments to be loaded into registers before a wave starts (the compiler can
@@ -256,27 +257,68 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   return v;
 }
 
+// Bounded chunks: whether the chunks with rows are dealt longest first.  It
+// evens out the bytes per XCD where many sequences have a few chunks each,
+// of lengths up to the bound apart (us per step, longest first against
+// sequence by sequence: B48 of 256 to 8192 rows, 3 splits, paged 51.5 and
+// 54.5, contiguous 42.9 and 44.8; B32 to 8192 rows, H16 G4 d 64, 8 splits,
+// 14.0 and 15.3; B64 to 8192 rows, H16 G2 d 128, 8 splits, 26.8 and 28.2).
+// With more splits the chunks are alike already and finding the order costs
+// more than it gives (B64 to 32K rows, 20 splits: 46.0 and 44.9), nor does it
+// pay with few sequences (B16 to 4096 rows, 8 splits: 18.7 and 18.1).
+__device__ __forceinline__ bool longest_first(const DecodeArgs& p) { return p.B >= 32 && p.B <= 64 && p.S <= 8; }
+
 // Bounded chunks: slot i of the B * S (sequence, split) slots.  Slots are
-// numbered splits with rows first (sequence-major), then the empty splits,
-// so the dispatcher hands out every chunk with rows before any workgroup
-// that only records an empty split.  The map is a bijection of [0, B S)
-// onto the slots, found by every wave of the workgroup from the lengths in
-// two levels: lane l first sums the counts of the k = ceil(B / 64)
-// sequences [l k, l k + k) (independent loads), a scan over the lanes
-// finds the block holding slot i, and for k > 1 a second scan over that
-// block's sequences (64 at a time) finds the sequence.  empty: the slot
-// has no rows.
+// numbered splits with rows first, then the empty splits, so the dispatcher
+// hands out every chunk with rows before any workgroup that only records an
+// empty split.  The map is a bijection of [0, B S) onto the slots, found by
+// every wave of the workgroup from the lengths.
+//  - Longest first (up to 64 sequences, one per lane; a sequence's chunks are
+//    equal; ties by sequence): each lane adds up the chunks of the sequences
+//    before its own, reading the others' lanes.
+//  - Sequence-major otherwise, in two levels: lane l first sums the counts of
+//    the k = ceil(B / 64) sequences [l k, l k + k) (independent loads), a scan
+//    over the lanes finds the block holding slot i, and for k > 1 a second
+//    scan over that block's sequences (64 at a time) finds the sequence.
+// empty: the slot has no rows.
 __device__ __forceinline__ void chunk_item(const DecodeArgs& p, int i, int& b, int& s, bool& empty) {
   const int lane = threadIdx.x & 63;
   const int k = (p.B + 63) >> 6;
-  int n_sum = 0, nb = 0;
+  int n_sum = 0, nb = 0, rows = 0;
 #pragma unroll 4
   for (int j = 0; j < k; ++j) {
-    n_sum += chunk_count(p, lane * k + j);
-    nb += lane * k + j < p.B ? 1 : 0;
+    const int bb = lane * k + j;
+    int L = bb < p.B ? p.lens[bb] : 0;
+    L = L < 0 ? 0 : (L > p.t_max ? p.t_max : L);
+    const int n = L > 0 ? split_count(L, p.S, p.split_rows) : 0;
+    n_sum += n;
+    nb += bb < p.B ? 1 : 0;
+    rows = L;                                  // k = 1: this lane's sequence
   }
-  const int F = wave_sum_int(n_sum);
+  const int F = __builtin_amdgcn_readfirstlane(wave_sum_int(n_sum));   // uniform, so b and s stay scalar
   const bool full = i < F;                     // a split with rows
+  empty = !full;
+  b = 0;
+  s = 0;
+  if (k == 1 && full && longest_first(p)) {
+    // one key per sequence: the rows of its chunks above the lane
+    const int chunk = n_sum > 0 ? rows / n_sum : 0;
+    const unsigned key = (unsigned)(chunk < (1 << 25) - 1 ? chunk : (1 << 25) - 1) << 6 | (unsigned)(63 - lane);
+    int before = 0;
+    for (int j0 = 0; j0 < p.B; j0 += 8) {      // (lanes past the batch hold no chunks)
+#pragma unroll
+      for (int j = j0; j < j0 + 8; ++j) {
+        const unsigned kj = (unsigned)__builtin_amdgcn_readlane((int)key, j);
+        const int nj = __builtin_amdgcn_readlane(n_sum, j);
+        before += kj > key ? nj : 0;
+      }
+    }
+    const unsigned long long hit = __ballot(n_sum > 0 && before <= i && i < before + n_sum);
+    const int j = hit != 0ull ? __builtin_ctzll(hit) : 0;   // exactly one lane
+    b = j;
+    s = i - __builtin_amdgcn_readlane(before, j);
+    return;
+  }
   const int kk = full ? i : i - F;
   // slots of the category per sequence: its splits with rows, or the rest
   auto pick = [&](int n, int valid) { return full ? n : valid * p.S - n; };
@@ -287,8 +329,6 @@ __device__ __forceinline__ void chunk_item(const DecodeArgs& p, int i, int& b, i
   // the slot's split within its sequence: the local-th with rows, or the
   // local-th empty one after those
   auto split_of = [&](int n, int local) { return full ? local : n + local; };
-  b = 0;
-  s = 0;
   if (k == 1) {                                // one sequence per lane: found
     b = __builtin_amdgcn_readfirstlane(j1);
     s = __builtin_amdgcn_readfirstlane(split_of(__shfl(n_sum, j1, 64), kk - base));
@@ -310,16 +350,15 @@ __device__ __forceinline__ void chunk_item(const DecodeArgs& p, int i, int& b, i
       base = __shfl(incl, 63, 64);
     }
   }
-  empty = !full;
 }
 
 __device__ __forceinline__ bool work_item(const DecodeArgs& p, int& b, int& s, int& g, bool& empty) {
   const int x = blockIdx.x;
   empty = false;
   if (p.split_rows > 0) {
-    const int slot = x >> 3;                   // the workgroup's place on its XCD (x mod 8)
+    const int slot = x >> 3, r = slot / p.G;   // the workgroup's place on its XCD (x mod 8)
     g = slot % p.G;
-    const int i = 8 * (slot / p.G) + (x & 7);
+    const int i = 8 * r + ((r & 1) ? 7 - (x & 7) : (x & 7));
     if (i >= p.B * p.S) return false;
     chunk_item(p, i, b, s, empty);
     return true;

@@ -806,6 +806,20 @@ def test_bounded_chunk_slots_large_batch(cfg, fused):
             assert err <= QUALITY["bf16"], (S, rows, s, err)
 
 
+# Batches whose chunks are dealt longest first (32 to 64 sequences, at most
+# eight splits), with empty sequences and equal chunks among them.
+LONGEST_FIRST_CHUNKS = [
+    (33, 512, 8, 2, 64, 64, 16, [(3, 192), (7, 64), (1, 32)]),
+    (63, 256, 4, 1, 128, 64, 8, [(5, 64), (3, 32)]),
+]
+
+
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("cfg", LONGEST_FIRST_CHUNKS, ids=lambda c: f"B{c[0]}")
+def test_bounded_chunk_slots_longest_first(cfg, fused):
+    test_bounded_chunk_slots_large_batch(cfg, fused)
+
+
 # Even splits with B * S not a multiple of 8: the split-major slots in
 # contiguous XCD ranges, some slot's groups on two XCDs.  (B, H, G, S):
 # 21 x 8 streams (>= half the CUs: four waves per workgroup), and 5 x 8 x 3
