@@ -417,12 +417,11 @@ def rope_comparison(args, w, inp, S, split_rows, dev, caches, stream):
 def prefill_kernel_name(w, N: int) -> str:
     """The prefill kernel gva_prefill_attention launches for one sequence
     of N prompt rows at w's head shapes (the library's rule, for the label):
-    columns per wave at d_v = 128 and d_r <= 32 once its workgroups number
-    2 per CU (4 at H/G = 8), else the tile-split kernel."""
-    hpg = w.n_heads // w.n_groups
-    items = w.n_groups * -(-N // (128 // hpg))
-    per_wave = w.d_v == 128 and w.d_r <= 32 and items >= (4 if hpg >= 8 else 2) * gva.device_cu_count()
-    return "prefill_vt_kernel" if per_wave else "prefill_bf16_kernel"
+    the shared-tiles kernel from 3/4 workgroup of 128 columns per CU, or for
+    caches of at most 1024 rows, else the tile-split kernel."""
+    items = w.n_groups * -(-N // (128 // (w.n_heads // w.n_groups)))
+    shared = 4 * items >= 3 * gva.device_cu_count() or w.t_max <= 1024
+    return "prefill_lds_kernel" if shared else "prefill_bf16_kernel"
 
 
 def prefill_comparison(args, w, caches, dev, stream):

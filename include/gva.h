@@ -25,7 +25,7 @@
  * GVA with ordinary RoPE (keys reconstructed and rotated per position, the
  * variant that cannot absorb M_h) has gva_rope_decode_attention, as a
  * contrast workload.  A prompt is attended causally in one pass with
- * gva_prefill_absorb + gva_prefill_attention (gva_gqa_prefill_attention
+ * gva_prefill, or gva_prefill_absorb + gva_prefill_attention (gva_gqa_prefill_attention
  * for the matched GQA baseline).
  *
  * Conventions shared by every call
