@@ -4,6 +4,7 @@
 // for launches of few workgroups), gva_prefill, gva_prefill_attention and the
 // matched-GQA baseline gva_gqa_prefill_attention.
 
+#include <cfloat>
 #include <type_traits>
 
 #include "gva_common.h"
@@ -675,7 +676,10 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
   }
 
   f32x16 acc[NIB];
-  float m_run = 0.f, l_run = 0.f;
+  // the running maximum starts below every score but -inf (a row hidden from
+  // the column): an exponential against it is 0, and the first score that
+  // counts replaces it
+  float m_run = -FLT_MAX, l_run = 0.f;
 #pragma unroll
   for (int ib = 0; ib < NIB; ++ib)
 #pragma unroll
@@ -783,11 +787,10 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
       const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
       mt = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     }
-    // The maximum is the first tile's, and moves when a column's tile
-    // maximum exceeds it by more than kLazyMax (log2 units).
+    // The maximum is the first tile's with a row that counts, and moves when
+    // a column's tile maximum exceeds it by more than kLazyMax (log2 units).
     if (FIRST || __ballot(mt > m_run + kLazyMax) != 0) {
-      float m_new = FIRST ? mt : fmaxf(mt, m_run);
-      if (mt == -INFINITY) m_new = m_run;      // no row of the tile is the column's
+      const float m_new = fmaxf(mt, m_run);
       if constexpr (!FIRST) {
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         l_run *= alpha;

@@ -1450,6 +1450,37 @@ def test_prefill_shared_tiles_matches_oracle(B, hpg, G, dv, dc, dr, N, prefix, s
     _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label + " two calls")
 
 
+# Cached rows hidden through their positional keys: the type's lowest value
+# against a large query entry overflows their scores to -inf.  (B, H/G, G,
+# d_v, N, capacity): two sets of waves, one set, and the tile-split kernel.
+PREFILL_HIDDEN_ROWS = [(8, 8, 4, 64, 100, 176), (8, 4, 8, 128, 225, 304), (2, 2, 2, 128, 33, 1040)]
+
+
+@pytest.mark.parametrize("B,hpg,G,dv,N,T", PREFILL_HIDDEN_ROWS)
+def test_prefill_first_tiles_hidden(B, hpg, G, dv, N, T):
+    # the first two key tiles hidden from every column, the scores of the
+    # rows after them near -30 (log2): the running maximum has to start at
+    # the first row that counts, or every weight underflows
+    dr = 16
+    w = gva_inputs.Workload("prefill_hidden", B, T, hpg * G, G, dv, dv, dr, dtype="bf16")
+    lens = torch.tensor([N + 70 - (b % 3) for b in range(B)], dtype=torch.int32)
+    inp = gva_inputs.make_inputs(w, 73, lens=lens)
+    q = gva_inputs.prefill_queries(w, 73, N)
+    q[..., dv:] = 0.0
+    q[..., dv + dr - 2] = 40.0                 # the slowest pair: hardly turned at these positions
+    inp["kr"].zero_()
+    inp["kr"][..., dr - 2] = -0.5 * math.sqrt(dv + dr)
+    inp["kr"][:, :64, dr - 2] = torch.finfo(torch.bfloat16).min
+    label = f"prefill hidden rows B{B} hpg{hpg} G{G} d{dv} N{N}"
+    note(f"{label}: oracle")
+    o_ref, lse_ref = oracle.prefill(q, inp["m"], inp["v"], inp["kr"], lens, rope_base=w.rope_base)
+    dev = upload({k: inp[k] for k in ("m", "v", "kr", "lens")})
+    note(f"{label}: GPU")
+    o, lse = gva.prefill(dims_of(w), q.cuda(), dev["m"], dev["v"], dev["kr"], dev["lens"])
+    torch.cuda.synchronize()
+    _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label)
+
+
 def test_prefill_after_append_of_the_prompt():
     # Algorithm 1's append for every prompt row (gva_append_kv), then the
     # prefill over the appended caches, against the oracle doing the same
