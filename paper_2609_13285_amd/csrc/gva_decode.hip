@@ -42,6 +42,7 @@
 // exactly the B-operand layout of the P.V product, so the softmax needs no
 // cross-lane traffic except the max over the four 16-lane rows.
 
+#include <cfloat>
 #include <mutex>
 #include <type_traits>
 
@@ -915,8 +916,8 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves ? 2 : 1)
 // padded by 16 bytes so that neither side conflicts), which moves bits and
 // costs less than products with an identity would (4 of 16 x 16 x 4 per
 // block).  NC and NRC are d_v and d_r in 16-column chunks, rounded up: pieces
-// past either re-read a valid one against a zero query and their outputs are
-// not written.
+// past either re-read a valid one, are zeroed and meet a zero query, and their
+// outputs are not written.
 // The matrix cores take 256 cycles per 16 x 16 block of a tile (9.8 TB/s of
 // rows at 2.4 GHz), whatever the heads per group, so the kernel is bound by
 // latency at the sizes fp32 is used at.  The kernel it replaced scored one
@@ -1158,11 +1159,14 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1)
   }
   __syncthreads();                             // the queries' LDS is the waves' transposition tiles from here on
 
-  float m_run = -INFINITY, l_run = 0.f;
+  // the running maximum starts below every score but -inf (a row hidden from
+  // the query): an exponential against it is 0, never -inf - -inf
+  float m_run = -FLT_MAX, l_run = 0.f;
   f32x4 acc[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) acc[c] = zero4;
   float* const tr = lds + w * 16 * PITCH;
+  const bool ragged = DV % 16 != 0 || DR % 16 != 0;   // the last chunks hold pieces past the row
 
   auto compute_tile = [&](TileF& t, int row0, int row_end) __attribute__((always_inline)) {
     const bool tail = row0 + kF32TileRows > row_end;
@@ -1172,6 +1176,12 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1)
       for (int c = 0; c < NC; ++c) t.v[c] = dead ? zero4 : t.v[c];
 #pragma unroll
       for (int c = 0; c < NRC; ++c) t.k[c] = dead ? zero4 : t.k[c];
+    }
+    if (ragged) {                              // an infinity read again there would meet the query's zero
+#pragma unroll
+      for (int c = 0; c < NC; ++c) t.v[c] = 16 * c + 4 * qd < DV ? t.v[c] : zero4;
+#pragma unroll
+      for (int c = 0; c < NRC; ++c) t.k[c] = 16 * c + 4 * qd < DR ? t.k[c] : zero4;
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4*>(tr + n * PITCH + 16 * c + 4 * qd) = t.v[c];
@@ -1239,6 +1249,7 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1)
 
   // ---- merge the waves and write this split's partial
   l_run = sum_over_rows(l_run);
+  if (l_run == 0.f) m_run = -INFINITY;         // no row counted
   __syncthreads();                             // the transposition tiles are the records below
   if (active) {
     float* rec = lds + (w * kF32MaxHpg + n) * PITCH;

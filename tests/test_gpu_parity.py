@@ -199,6 +199,28 @@ def test_f32_chunk_and_tile_edges(B, hpg, G, dv, dc, dr, T):
             assert torch.equal(gva.untiled(dev["kr"].cpu())[b, L - 1], k_ref[b, L - 1]) or dr == 0
 
 
+@pytest.mark.parametrize("dr,hidden", [(12, float("-inf")), (16, torch.finfo(torch.float32).min)])
+def test_f32_rows_hidden_by_their_positional_keys(dr, hidden):
+    # a whole 16-row tile (one wave's only one, or its first) with scores of
+    # -inf, the positional key's last chunk half used or full: those rows do
+    # not count, and the zeros past d_r do not meet the infinities
+    T = 176
+    w = gva_inputs.Workload("f32_hidden", 3, T, 6, 2, 20, 24, dr, dtype="f32")
+    lens = torch.tensor([T, 90, 33], dtype=torch.int32)
+    inp = gva_inputs.make_inputs(w, 79, lens=lens)
+    inp["q"][..., 24:] = 0.0
+    inp["q"][..., 24 + dr - 2] = 40.0          # the slowest pair: hardly turned at these positions
+    inp["kr"].zero_()
+    inp["kr"][:, :16, dr - 2] = hidden
+    o_ref, lse_ref = oracle.decode(inp["q"], inp["m"], inp["v"], inp["kr"], lens, rope_base=w.rope_base)
+    dev = upload(inp)
+    for S, fused in ((1, True), (1, False), (2, True)):
+        label = f"f32 hidden rows dr{dr} S{S} fused={fused}"
+        note(label)
+        o, lse, _, _ = run_decode(w, dev, S, fused=fused)
+        _check(w, o, lse, o_ref, lse_ref, label)
+
+
 # -------------------------------------------------------------- edge cases
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_ragged_and_degenerate_lengths(dtype):
