@@ -325,7 +325,9 @@ int gva_prefill_absorb(const gva_dims* dims, int32_t n_new, const void* q, const
  * bandwidth-bound decode step (which keeps query and weights as bf16
  * high+low pairs): the queries enter the matrix cores as bf16, the softmax
  * weights and the value rows as fp16 (exact for bf16 values of magnitude
- * 2^-14 .. 65504; value entries must stay below 65504 in magnitude).
+ * 2^-14 .. 65504; value entries must stay below 65504 in magnitude).  The
+ * queries keep a bf16 low part beside it, and where the launch is large
+ * enough to share key tiles the weights of the first 128 rows a low fp16 one.
  * o [B][n_new][H][d_v] fp32, lse [B][n_new][H] fp32; the caches are read
  * only.  Supported: bf16, d_v in {64, 128}, d_r a multiple of 8 (<= 64),
  * H/G in {1, 2, 4, 8}, T % 16 == 0; other valid shapes:

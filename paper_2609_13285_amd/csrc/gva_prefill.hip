@@ -478,6 +478,17 @@ __device__ __forceinline__ void wait_copies() {   // until at most N of this wav
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// The weights of the first kLowRows rows take a second, low part through P.V.
+// A short row of outputs is a sum of few weights, whose roundings to fp16 then
+// do not average out: with one running maximum per column (the tile-split
+// kernel has four, one per wave, and each makes one weight exact) the error of
+// short prompts was 5 to 16% above the tile-split kernel's.  With it the
+// rounding of the first 128 rows, where those four lie, is gone (off a 64-bit
+// evaluation, tile-split, without and with it: four 2048-token prompts at H16
+// G4 d 64/16 1.01e-4, 1.10e-4, 7.3e-5; 512 tokens 1.17e-4, 1.32e-4, 6.2e-5).
+// It costs the 350M prompts 77.2 -> 80.9 us, 8192 tokens 752 -> 766.
+constexpr int kLowRows = 128;
+
 // row of a 32-row tile in score register r of a lane in half h
 __device__ __forceinline__ constexpr int score_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
@@ -691,10 +702,35 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
     return *reinterpret_cast<const f16x8*>(vt_lane + vbuf * Cfg::VT_BYTES + k * 1024);
   };
 
-  // element r of the softmax weights of scores sc
+  // element r of the softmax weights of scores sc; the tile's sum joins the
+  // running one when it is whole (a running sum over single weights has
+  // sixteen times the roundings)
+  float tile_sum = 0.f;
   auto exps = [&](const f32x16& sc, float (&pr)[16], int r) {
     pr[r] = __builtin_amdgcn_exp2f(sc[r] - m_run);
-    l_run += pr[r];
+    tile_sum = r == 0 ? pr[r] : tile_sum + pr[r];
+    if (r == 15) l_run += tile_sum;
+  };
+  // What a tile's fp16 weights leave over, through the same V^T: run for the
+  // tiles below kLowRows, ahead of the tile's P.V.
+  auto add_low = [&](const f32x16& sc, int vbuf) __attribute__((always_inline)) {
+    float m = m_run;                           // opaque: formed again here, not kept for the tile's own P.V
+    asm volatile("" : "+v"(m));
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {              // a half at a time: few registers beside the loop's
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = __builtin_amdgcn_exp2f(sc[8 * c + e] - m);
+      const f16x8 hi = to_f16x8(x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] -= (float)hi[e];
+      const f16x8 lo = to_f16x8(x);
+#pragma unroll
+      for (int ib = 0; ib < NIB; ++ib) {
+        acc[ib] = mfma32(vt_piece(vbuf, 2 * ib + c), lo, acc[ib]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   };
   // One tile: scores sn of tile j, beside them the softmax weights of the
   // tile before (scores sp), then that tile's P.V, beside it tile j's maxima.
@@ -704,6 +740,9 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
   auto step = [&](auto first_tag, int j, int buf, const f32x16& sp, f32x16& sn) __attribute__((always_inline)) {
     constexpr bool FIRST = decltype(first_tag)::value;
     const int row0 = tile_row(j);
+    if constexpr (!FIRST) {
+      if (tile_row(j - 1) < kLowRows) add_low(sp, (j & 1) ^ 1);
+    }
     copy_tile(tile_row(j + 2), buf == 0 ? 2 : buf - 1);
     const char* vtile = grp_lds + buf * Cfg::TILE_BYTES;
     const char* ktile = vtile + Cfg::V_BYTES;
@@ -804,6 +843,7 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
     __builtin_amdgcn_s_barrier();
   };
   auto last = [&](const f32x16& sp) {          // the last tile's weights and P.V
+    if (tile_row(nit - 1) < kLowRows) add_low(sp, (nit - 1) & 1);
     float pr[16];
     f16x8 bn[2];
 #pragma unroll

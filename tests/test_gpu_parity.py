@@ -1472,6 +1472,38 @@ def test_prefill_shared_tiles_matches_oracle(B, hpg, G, dv, dc, dr, N, prefix, s
     _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label + " two calls")
 
 
+@pytest.mark.parametrize("B,hpg,G,dv,N,gqa", [(8, 8, 4, 64, 100, False), (16, 4, 8, 128, 97, False),
+                                              (8, 2, 8, 128, 128, True), (16, 4, 8, 64, 127, True)])
+def test_prefill_low_parts_of_the_first_rows(B, hpg, G, dv, N, gqa):
+    # Prompts of at most 128 rows in the shared-tiles kernel, whose weights
+    # all take a low part: what is left is the queries' high + low pairs,
+    # 2^-17 of each entry, so logits near 1 are off by less than 2^-17 and o
+    # by about as much; twice that is allowed (weights rounded once to fp16
+    # leave 1.2e-4).
+    n_cu = gva.device_cu_count()
+    items = B * G * -(-N // (128 // hpg))
+    assert 4 * items >= (2 if gqa and dv == 128 else 3) * n_cu, "the shape must take this kernel"
+    w = gva_inputs.Workload("prefill_low", B, 128, hpg * G, G, dv, dv, 0 if gqa else 16, dtype="bf16", gqa=gqa)
+    lens = torch.tensor([N + b % 2 for b in range(B)], dtype=torch.int32).clamp(max=128)
+    inp = gva_inputs.make_inputs(w, 83, lens=lens)
+    q = gva_inputs.prefill_queries(w, 83, N, gqa=gqa)
+    label = f"prefill low parts B{B} hpg{hpg} G{G} d{dv} N{N} gqa={gqa}"
+    note(f"{label}: GPU")
+    dev = upload({k: inp[k] for k in (("v", "k_gqa", "lens") if gqa else ("m", "v", "kr", "lens"))})
+    if gqa:
+        o = torch.empty(B, N, w.n_heads, dv, dtype=torch.float32, device="cuda")
+        lse = torch.empty(B, N, w.n_heads, dtype=torch.float32, device="cuda")
+        gva.gva_gqa_prefill_attention(dims_of(w), N, q.cuda(), dev["k_gqa"], dev["v"], dev["lens"], o, lse)
+        o_ref = torch.stack([oracle.gqa_decode(q[:, i].contiguous(), inp["k_gqa"], inp["v"], lens - N + i + 1,
+                                               d_k=dv)[0] for i in range(N)], 1)
+    else:
+        o, lse = gva.prefill(dims_of(w), q.cuda(), dev["m"], dev["v"], dev["kr"], dev["lens"])
+        o_ref, _ = oracle.prefill(q, inp["m"], inp["v"], inp["kr"], lens, rope_base=w.rope_base)
+    err = float((o.cpu().double() - o_ref).norm() / o_ref.norm())
+    note(f"{label}: relative error {err:.2e}")
+    assert err <= 2.0 ** -16, (label, err)
+
+
 # Cached rows hidden through their positional keys: the type's lowest value
 # against a large query entry overflows their scores to -inf.  (B, H/G, G,
 # d_v, N, capacity): two sets of waves, one set, and the tile-split kernel.
