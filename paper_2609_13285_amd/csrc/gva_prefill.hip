@@ -466,12 +466,11 @@ __device__ __forceinline__ i32x4 buffer_desc(const void* p, int bytes) {
 // address dst.  In asm because the compiler, which cannot tell the tile
 // buffers apart, would otherwise drain every copy in flight before each LDS
 // read; the kernel waits for its own copies (wait_copies) before the barrier
-// that hands a tile over.  The copy writes no register but m0, which the
-// compiler keeps nothing in across statements.
+// that hands a tile over.  The copy writes no register but m0.
 __device__ __forceinline__ void copy_kb(i32x4 desc, uint32_t dst, int voff, int soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                ::"s"(dst), "v"(voff), "s"(desc), "s"(soff)
-               : "memory");
+               : "memory", "m0");
 }
 template <int N>
 __device__ __forceinline__ void wait_copies() {   // until at most N of this wave's copies are in flight
@@ -488,6 +487,14 @@ __device__ __forceinline__ void wait_copies() {   // until at most N of this wav
 // G4 d 64/16 1.01e-4, 1.10e-4, 7.3e-5; 512 tokens 1.17e-4, 1.32e-4, 6.2e-5).
 // It costs the 350M prompts 77.2 -> 80.9 us, 8192 tokens 752 -> 766.
 constexpr int kLowRows = 128;
+
+// The workgroup's barrier, which alone orders no memory access for the
+// compiler: accesses stay on their side of it.
+__device__ __forceinline__ void tile_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 // row of a 32-row tile in score register r of a lane in half h
 __device__ __forceinline__ constexpr int score_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
@@ -840,7 +847,7 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
     }
     wait_copies<Cfg::COPIES>();                // the next tile has landed (the one after it may be in flight)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's V^T block is in LDS
-    __builtin_amdgcn_s_barrier();
+    tile_barrier();
   };
   auto last = [&](const f32x16& sp) {          // the last tile's weights and P.V
     if (tile_row(nit - 1) < kLowRows) add_low(sp, (nit - 1) & 1);
@@ -855,7 +862,7 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
   };
 
   wait_copies<Cfg::COPIES>();
-  __builtin_amdgcn_s_barrier();
+  tile_barrier();
   if (nit > 0) {
     f32x16 s0, s1;                             // the scores of even and odd tiles
     step(std::true_type{}, 0, 0, s0, s0);
