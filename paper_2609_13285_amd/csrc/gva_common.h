@@ -75,7 +75,6 @@ struct DecodeArgs {
   int32_t B, H, G, d_v, d_c, d_r, t_max, S;
   int32_t split_rows;     // fixed rows per split (0: the even rule)
   float scale_log2;       // score scale * log2(e): softmax runs in base 2
-  int32_t fused;
   const int32_t* block_table;   // paged caches: [B][max_pages] page ids
   int32_t page_rows, max_pages, n_pages;
 };

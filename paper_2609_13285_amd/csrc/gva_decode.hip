@@ -1769,7 +1769,6 @@ int decode_attention_impl(const gva_dims* dims, const gva_paging* paging, const 
   p.a.S = num_splits;
   p.a.split_rows = split_rows;
   p.a.scale_log2 = scale_log2(dims);
-  p.a.fused = fused ? 1 : 0;
   p.a.block_table = block_table;
   p.a.page_rows = paging ? paging->page_rows : 0;
   p.a.max_pages = paging ? paging->max_pages : 0;
