@@ -496,6 +496,14 @@ __device__ __forceinline__ void tile_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// LDS written by this wave's lanes is readable by its others from here on,
+// and what they have read may be written again.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // row of a 32-row tile in score register r of a lane in half h
 __device__ __forceinline__ constexpr int score_row(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
@@ -515,6 +523,7 @@ struct PrefillCfg {
   static constexpr int COPIES = KB / 4 * (GQA ? 2 : 1) + (NRC > 0 ? 1 : 0);   // per wave and tile
   static constexpr int MERGE_BYTES = KS > 1 ? kWaves * 64 * (NIB * 16 + 2) * 4 : 0;
   static constexpr int LDS = KS * GROUP_BYTES > MERGE_BYTES ? KS * GROUP_BYTES : MERGE_BYTES;
+  static_assert(GROUP_BYTES >= kWaves * 32 * 36 * 4, "the outputs pass through the tiles' LDS");
 };
 
 template <int DV, int NRC, bool GQA, int KS>
@@ -913,23 +922,42 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
       for (int r = 0; r < 16; ++r) acc[ib][r] = acc[ib][r] * a0 + rec[64 * (2 + 16 * ib + r)] * a1;
   } else {
     wait_copies<0>();
+    __syncthreads();                           // every wave is done with the tiles
   }
-  if (i_col >= p.N) return;
+  // A lane holds 16 bytes of its column at a time, two lanes of a column 32:
+  // as they lie, streaming stores of parts of a line, which the memory has to
+  // merge.  They go through the wave's own LDS a 32-wide block at a time and
+  // leave as whole 128-byte lines.
   const bool seen = pos >= 0 && !(l_run == 0.f);
   const float inv = seen ? 1.f / l_run : 0.f;
+  constexpr int OP = 36;                       // floats per padded LDS row
+  float* const ob = reinterpret_cast<float*>(lds + w * (KS > 1 ? Cfg::MERGE_BYTES / kWaves : 32 * OP * 4));
 #pragma unroll
-  for (int ib = 0; ib < NIB; ++ib)
+  for (int ib = 0; ib < NIB; ++ib) {
+    wave_fence();                              // the block before has been read
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
       f32x4 o;
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) o[jj] = acc[ib][4 * r4 + jj] * inv;
       if (!seen) o = f32x4{0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<f32x4*>(ob + n * OP + 8 * r4 + 4 * h) = o;
+    }
+    wave_fence();
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int col = 8 * it + (lane >> 3);
+      const f32x4 o = *reinterpret_cast<const f32x4*>(ob + col * OP + 4 * (lane & 7));
+      const int i = wpos + (hpg == 8 ? col & 15 : col);
+      const int hd = hpg == 8 ? g * hpg + 2 * w + (col >> 4) : head;
       // written once and not read again here: kept out of the L2, which holds
       // the group's key and value rows
-      __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(p.o + qrow * DV + 32 * ib + 8 * r4 + 4 * h));
+      if (i < p.N)
+        __builtin_nontemporal_store(
+            o, reinterpret_cast<f32x4*>(p.o + (((int64_t)b * p.N + i) * p.H + hd) * DV + 32 * ib + 4 * (lane & 7)));
     }
-  if (h == 0) p.lse[qrow] = seen ? (m_run + log2f(l_run)) * kLn2 : -INFINITY;
+  }
+  if (h == 0 && i_col < p.N) p.lse[qrow] = seen ? (m_run + log2f(l_run)) * kLn2 : -INFINITY;
 }
 
 template <int DV, int KS>
