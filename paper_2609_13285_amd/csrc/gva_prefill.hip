@@ -1005,37 +1005,74 @@ PrefillFn pick_prefill(int hpg, int dv, int d_r, bool gqa) {
 }
 
 // Which kernel a prompt takes: the sets of four waves per workgroup of
-// prefill_lds_kernel, or 0 for the tile-split kernel.  By the workgroups of
-// 128 columns against the CUs:
-//  - two per CU and more: one set (two workgroups per CU; 2048 tokens at H32
-//    G8 d 128, 512 workgroups: 81 us, 92 with two sets);
-//  - from 3/4 per CU: two sets, so that each SIMD has two waves (H16 G4 d 64,
-//    2048 tokens, 256 workgroups: 41 us, 48 with one set, 50 tile-split; H32
-//    G8, 768 rows after 8000, 192 workgroups: 142, 165, 159);
-//  - fewer: the tile-split kernel, whose workgroups are a half to an eighth
-//    the size and split the keys over the four waves (H32 G8, 512 rows after
-//    8000, 128 workgroups: 110 us, 133 with two sets; 64 rows after 8000: 68
-//    and 125) -- for the baseline at d_v = 128, whose tile-split workgroups
-//    hold only 16 columns, below 1/2 (256 rows after 8000: 70 and 111; 768:
-//    188 and 125).  Caches of at most 1024 rows keep the one-set kernel: a
-//    workgroup's chain of tiles is then short, and the one launch with the
-//    absorption inside it is what counts (512 tokens, 128 workgroups: 29 and
-//    36 us).
-int prefill_sets(const gva_dims* d, int n_new, bool gqa) {
+// prefill_lds_kernel, or 0 for the tile-split kernel, whose workgroups are a
+// half to an eighth the size and split the keys over the four waves.  By its
+// workgroups of 128 columns against the CUs (us below are single calls):
+//  - two per CU and more: one set, two workgroups per CU (2048 tokens at H32
+//    G8 d 128, 512 workgroups: 77 us, 88 with two sets, 123 tile-split);
+//  - from 3/4 per CU (the baseline at d_v = 128, whose tile-split workgroups
+//    hold only 16 columns but whose chains are half as long: 1/2): two sets,
+//    so that each SIMD has two waves (H16 G4 d 128, 2048 tokens, 256
+//    workgroups: 54, 58 and 70; H32 G8, 768 rows after 3328, 192 workgroups:
+//    90, 102 and 108).  But the launch then takes as long as the longest
+//    block's keys, the tile-split one as long as all of them together, and the
+//    blocks of a prompt without a prefix average half the longest: counted in
+//    blocks of that average, long caches need more than 1/2 per CU (H3 G3 d
+//    128, 8192 tokens, 192 workgroups: 154 us, 127 tile-split; at 256, H4 G1,
+//    158 and 155; d_v = 64 from 8192 rows only, 4096 tokens with 192
+//    workgroups 59 and 66), the baseline 3/8, from 1024 rows on 7/16 (H8 G8
+//    d 128, 2048 tokens, 128 workgroups: 42 and 36; 512 after 1536: 42 and 46);
+//  - fewer: the tile-split kernel (H32 G8 d 128, 512 rows after 7680, 128
+//    workgroups: 128 us, 153 with two sets; baseline, 64 rows after 960: 12
+//    and 27), except where the cache is short, so that a workgroup's chain of
+//    tiles is, and at least 32 columns of a group have a query (a single row
+//    of 8 x 1 heads after 1023: 18 us tile-split, 29 with two sets).  At
+//    d_v = 64, whose tile-split workgroup starts slowly, up to 1024 rows, one
+//    set to 128 rows, or 256 with the absorption inside, and two sets past
+//    that (H32 G8, 512 tokens: 17 us, 30 tile-split; 64 rows after 960: 22
+//    and 28).  At d_v = 128 up to 128 rows, or 256 with the absorption's
+//    launch to save (H32 G8, 256 tokens: 19 and 24), to 512 the larger the
+//    prompt (512 tokens, 128 workgroups: 25 and 33; H4 G2, 16 workgroups: 24
+//    and 22), and never for the baseline (128 tokens: 11 us, 9 tile-split).
+enum class Prompt { kAttention, kWhole, kGqa };   // absorbed queries, raw ones (gva_prefill), the baseline
+
+struct PrefillPlan {
+  int sets;
+  bool inside;                                 // kWhole: the absorption inside the attention launch
+};
+
+PrefillPlan prefill_plan(const gva_dims* d, int n_new, Prompt kind) {
   const int hpg = d->n_heads / d->n_groups;
-  if (hpg > 8) return 0;                       // no kernel takes it
+  if (hpg > 8) return {0, false};              // no kernel takes it
+  const bool whole = kind == Prompt::kWhole;
   const int rows = kPrefillCols / hpg;         // positions per workgroup
-  const long long items = (long long)d->batch * d->n_groups * ((n_new + rows - 1) / rows);
-  const long long n_cu = device_cu_count();
-  if (items >= 2 * n_cu) return 1;
-  if (4 * items >= (gqa && d->d_v >= 128 ? 2 : 3) * n_cu) return 2;
-  return d->t_max <= 1024 ? 1 : 0;
+  const long long items = (long long)d->batch * d->n_groups * (((long long)n_new + rows - 1) / rows);
+  const long long n_cu = device_cu_count(), T = d->t_max;
+  if (items >= 2 * n_cu) return {1, whole};
+  // twice the blocks of average length: all rows' keys over those of the longest
+  const double mean2 = (double)items * (double)(2 * T - n_new) / (double)T;
+  bool two_sets;
+  if (kind == Prompt::kGqa && d->d_v >= 128)
+    two_sets = 4 * items >= 3 * n_cu ||
+               (2 * items >= n_cu && (T <= 512 || 8 * mean2 >= (T > 1024 ? 7 : 6) * (double)n_cu));
+  else
+    two_sets = 4 * items >= 3 * n_cu && (T < (d->d_v >= 128 || !whole ? 4096 : 8192) || mean2 > (double)n_cu);
+  if (two_sets) return {2, whole};
+  const bool cols32 = (long long)n_new * hpg >= 32;
+  if (d->d_v < 128) {
+    if (T <= (whole ? 256 : 128)) return {1, whole};
+    return {cols32 && T <= 1024 ? 2 : 0, cols32 && T <= 1024 && whole};
+  }
+  if (!cols32 || kind == Prompt::kGqa) return {0, false};
+  const int passes = hpg == 8 ? 2 : 1;         // of a wave's absorption
+  if (T <= (whole ? 256 : 128) || (whole && T <= 512 && passes * T * n_cu <= 2048 * items)) return {1, whole};
+  return {0, false};
 }
 
 // The launch behind gva_prefill_attention, gva_prefill (raw query q and maps
 // m in place of q_abs and q_rot) and, with k_gqa given,
-// gva_gqa_prefill_attention.
-int prefill_impl(const gva_dims* dims, int32_t n_new, const float* q_abs, const float* q_rot, const void* q,
+// gva_gqa_prefill_attention, with the sets of its plan.
+int prefill_impl(int sets, const gva_dims* dims, int32_t n_new, const float* q_abs, const float* q_rot, const void* q,
                  const void* m, const void* v_cache, const void* kr_cache, const void* k_gqa, const int32_t* lens,
                  float* o, float* lse, void* stream, bool launch = true) {
   int st = check_dims(dims);
@@ -1057,7 +1094,6 @@ int prefill_impl(const gva_dims* dims, int32_t n_new, const float* q_abs, const 
   const int hpg = dims->n_heads / dims->n_groups;
   if (hpg != 1 && hpg != 2 && hpg != 4 && hpg != 8) return GVA_ERR_UNSUPPORTED;
   if (dims->d_v != 64 && dims->d_v != 128) return GVA_ERR_UNSUPPORTED;
-  const int sets = prefill_sets(dims, n_new, gqa);
   if (fused && sets == 0) return GVA_ERR_UNSUPPORTED;
   const PrefillFn fn = sets > 0 ? pick_prefill_lds(dims->d_v, d_r, gqa, sets) : pick_prefill(hpg, dims->d_v, d_r, gqa);
   if (fn == nullptr) return GVA_ERR_UNSUPPORTED;
@@ -1099,15 +1135,16 @@ int prefill_impl(const gva_dims* dims, int32_t n_new, const float* q_abs, const 
   return launch_status();
 }
 
-// Where gva_prefill's two launches keep the absorbed queries; bytes = 0 where
-// the absorption is fused.
+// gva_prefill's plan, and where its two launches keep the absorbed queries
+// (bytes = 0 with the absorption inside).
 struct PrefillLayout {
+  PrefillPlan plan;
   size_t q_rot, bytes;
 };
 
 void prefill_layout(const gva_dims* d, int n_new, PrefillLayout& L) {
-  L = PrefillLayout{0, 0};
-  if (prefill_sets(d, n_new, false) > 0) return;
+  L = PrefillLayout{prefill_plan(d, n_new, Prompt::kWhole), 0, 0};
+  if (L.plan.inside) return;
   const size_t rows = (size_t)d->batch * n_new * d->n_heads;
   L.q_rot = (rows * d->d_v * 4 + 255) / 256 * 256;
   L.bytes = L.q_rot + (rows * d->d_r * 4 + 255) / 256 * 256;
@@ -1120,7 +1157,10 @@ extern "C" {
 int gva_prefill_attention(const gva_dims* dims, int32_t n_new, const float* q_abs, const float* q_rot,
                           const void* v_cache, const void* kr_cache, const int32_t* lens, float* o,
                           float* lse, void* stream) {
-  return prefill_impl(dims, n_new, q_abs, q_rot, nullptr, nullptr, v_cache, kr_cache, nullptr, lens, o, lse, stream);
+  const int st = check_dims(dims);
+  if (st != GVA_OK) return st;
+  return prefill_impl(prefill_plan(dims, n_new, Prompt::kAttention).sets, dims, n_new, q_abs, q_rot, nullptr, nullptr,
+                      v_cache, kr_cache, nullptr, lens, o, lse, stream);
 }
 
 int gva_prefill_workspace_size(const gva_dims* dims, int32_t n_new, size_t* bytes) {
@@ -1147,23 +1187,29 @@ int gva_prefill(const gva_dims* dims, int32_t n_new, const void* q, const void* 
   PrefillLayout L;
   prefill_layout(dims, n_new, L);
   if (L.bytes == 0)
-    return prefill_impl(dims, n_new, nullptr, nullptr, q, m, v_cache, kr_cache, nullptr, lens, o, lse, stream);
+    return prefill_impl(L.plan.sets, dims, n_new, nullptr, nullptr, q, m, v_cache, kr_cache, nullptr, lens, o, lse,
+                        stream);
   if (workspace == nullptr || workspace_bytes < L.bytes || !aligned(workspace, 256)) return GVA_ERR_INVALID_ARG;
   float* q_abs = static_cast<float*>(workspace);
   float* q_rot = dims->d_r > 0 ? reinterpret_cast<float*>(static_cast<char*>(workspace) + L.q_rot) : nullptr;
   // every check of the second launch before the first is enqueued
-  st = prefill_impl(dims, n_new, q_abs, q_rot, nullptr, nullptr, v_cache, kr_cache, nullptr, lens, o, lse, stream, false);
+  st = prefill_impl(L.plan.sets, dims, n_new, q_abs, q_rot, nullptr, nullptr, v_cache, kr_cache, nullptr, lens, o, lse,
+                    stream, false);
   if (st != GVA_OK) return st;
   st = gva_prefill_absorb(dims, n_new, q, m, lens, q_abs, q_rot, stream);
   if (st != GVA_OK) return st;
-  return prefill_impl(dims, n_new, q_abs, q_rot, nullptr, nullptr, v_cache, kr_cache, nullptr, lens, o, lse, stream);
+  return prefill_impl(L.plan.sets, dims, n_new, q_abs, q_rot, nullptr, nullptr, v_cache, kr_cache, nullptr, lens, o, lse,
+                      stream);
 }
 
 int gva_gqa_prefill_attention(const gva_dims* dims, int32_t n_new, const float* q, const void* k_cache,
                               const void* v_cache, const int32_t* lens, float* o, float* lse,
                               void* stream) {
   if (k_cache == nullptr) return GVA_ERR_INVALID_ARG;
-  return prefill_impl(dims, n_new, q, nullptr, nullptr, nullptr, v_cache, nullptr, k_cache, lens, o, lse, stream);
+  const int st = check_dims(dims);
+  if (st != GVA_OK) return st;
+  return prefill_impl(prefill_plan(dims, n_new, Prompt::kGqa).sets, dims, n_new, q, nullptr, nullptr, nullptr, v_cache,
+                      nullptr, k_cache, lens, o, lse, stream);
 }
 
 }  // extern "C"

@@ -161,6 +161,32 @@ def test_prefill_validation():
     assert gva.gva_prefill_workspace_size(dims(**big), 512) == 0
 
 
+@pytest.mark.parametrize("kw,n_new,inside", [
+    # d_v = 128, few workgroups: by the cache's length against the prompt's size
+    (dict(n_heads=32, n_groups=8, t_max=1024), 64, False),
+    (dict(n_heads=32, n_groups=8, t_max=1024), 512, False),
+    (dict(n_heads=32, n_groups=8, t_max=512), 512, True),
+    (dict(n_heads=4, n_groups=2, t_max=512), 512, False),
+    (dict(n_heads=32, n_groups=8, t_max=256), 256, True),
+    (dict(n_heads=32, n_groups=8, t_max=256), 7, False),         # 28 columns of a group
+    # d_v = 64: to 1024 rows, or 256 whatever the columns
+    (dict(n_heads=32, n_groups=8, t_max=1024, d_v=64, d_c=64), 64, True),
+    (dict(n_heads=32, n_groups=8, t_max=1040, d_v=64, d_c=64), 64, False),
+    (dict(n_heads=8, n_groups=8, t_max=1024, d_v=64, d_c=64), 31, False),
+    (dict(n_heads=8, n_groups=8, t_max=256, d_v=64, d_c=64), 1, True),
+    # 192 workgroups: a whole long prompt, whose blocks average half the longest, against a chunk of one
+    (dict(n_heads=3, n_groups=3, t_max=8192), 8192, False),
+    (dict(n_heads=24, n_groups=6, t_max=8192), 1024, True),
+    (dict(n_heads=12, n_groups=3, t_max=2048), 2048, True),
+    (dict(n_heads=4, n_groups=1, t_max=4096, d_v=64, d_c=64, batch=2), 3072, True),
+])
+def test_prefill_routes(kw, n_new, inside):
+    # the workspace is for the absorbed queries of the two-launch route
+    # (workgroups against 256 compute units, without a GPU too)
+    d = dims(**{**dict(batch=1), **kw})
+    assert (gva.gva_prefill_workspace_size(d, n_new) == 0) == inside
+
+
 def test_pick_splits_is_host_only_and_bounded():
     d = dims(batch=32, n_heads=32, n_groups=8, t_max=8192)
     assert gva.gva_pick_splits(d, 8192, 0, 256) == (1, 0)       # 256 streams fill 256 CUs
