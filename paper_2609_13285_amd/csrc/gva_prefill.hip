@@ -1041,6 +1041,21 @@ struct PrefillPlan {
   bool inside;                                 // kWhole: the absorption inside the attention launch
 };
 
+// Whether gva_prefill absorbs inside the attention launch.  Each workgroup
+// then reads its heads' maps, each set of waves for itself and at H/G = 8 in
+// two passes: a launch of one workgroup or more per CU bears more of it
+// (`full`) than a small one, whose absorption's own launch is short (us,
+// inside and apart: H16 G2 d 128/512, 4 x 1024 tokens, one set 110 and 89,
+// 256 columns 73 and 72; H4 G4 d 64/1024 the same tokens 74 and 101; H32 G8
+// d 128/512, 512 tokens after 7680, two sets 222 and 211, 256 columns 203 and
+// 203; few workgroups: H16 G2 d 128/512, 256 tokens 49 and 24, d 128/128 23
+// and 20; H16 G4 d 64/512 22 and 19, d 64/256 16 and 17).
+bool absorb_inside(const gva_dims* d, int sets, bool full) {
+  const long long maps = (long long)(d->n_heads / d->n_groups == 8 ? 2 : 1) * sets;   // read per workgroup
+  if (full) return maps * d->d_c <= (maps == 1 ? 1024 : 640);
+  return maps * d->d_c * d->d_v <= 16384;
+}
+
 PrefillPlan prefill_plan(const gva_dims* d, int n_new, Prompt kind) {
   const int hpg = d->n_heads / d->n_groups;
   if (hpg > 8) return {0, false};              // no kernel takes it
@@ -1048,7 +1063,7 @@ PrefillPlan prefill_plan(const gva_dims* d, int n_new, Prompt kind) {
   const int rows = kPrefillCols / hpg;         // positions per workgroup
   const long long items = (long long)d->batch * d->n_groups * (((long long)n_new + rows - 1) / rows);
   const long long n_cu = device_cu_count(), T = d->t_max;
-  if (items >= 2 * n_cu) return {1, whole};
+  if (items >= 2 * n_cu) return {1, whole && absorb_inside(d, 1, true)};
   // twice the blocks of average length: all rows' keys over those of the longest
   const double mean2 = (double)items * (double)(2 * T - n_new) / (double)T;
   bool two_sets;
@@ -1057,15 +1072,17 @@ PrefillPlan prefill_plan(const gva_dims* d, int n_new, Prompt kind) {
                (2 * items >= n_cu && (T <= 512 || 8 * mean2 >= (T > 1024 ? 7 : 6) * (double)n_cu));
   else
     two_sets = 4 * items >= 3 * n_cu && (T < (d->d_v >= 128 || !whole ? 4096 : 8192) || mean2 > (double)n_cu);
-  if (two_sets) return {2, whole};
+  if (two_sets) return {2, whole && absorb_inside(d, 2, true)};
   const bool cols32 = (long long)n_new * hpg >= 32;
   if (d->d_v < 128) {
-    if (T <= (whole ? 256 : 128)) return {1, whole};
-    return {cols32 && T <= 1024 ? 2 : 0, cols32 && T <= 1024 && whole};
+    if (T <= (whole ? 256 : 128)) return {1, whole && absorb_inside(d, 1, false)};
+    if (cols32 && T <= 1024) return {2, whole && absorb_inside(d, 2, false)};
+    return {0, false};
   }
   if (!cols32 || kind == Prompt::kGqa) return {0, false};
   const int passes = hpg == 8 ? 2 : 1;         // of a wave's absorption
-  if (T <= (whole ? 256 : 128) || (whole && T <= 512 && passes * T * n_cu <= 2048 * items)) return {1, whole};
+  if (whole && T <= 512 && passes * T * n_cu <= 2048 * items && passes * d->d_c <= 256) return {1, true};
+  if (T <= (whole ? 256 : 128)) return {1, whole && absorb_inside(d, 1, false)};
   return {0, false};
 }
 

@@ -179,6 +179,16 @@ def test_prefill_validation():
     (dict(n_heads=24, n_groups=6, t_max=8192), 1024, True),
     (dict(n_heads=12, n_groups=3, t_max=2048), 2048, True),
     (dict(n_heads=4, n_groups=1, t_max=4096, d_v=64, d_c=64, batch=2), 3072, True),
+    # the maps' size against the launch's, in two passes at H/G = 8
+    (dict(n_heads=16, n_groups=2, t_max=1024, batch=4, d_c=320), 1024, True),
+    (dict(n_heads=16, n_groups=2, t_max=1024, batch=4, d_c=352), 1024, False),
+    (dict(n_heads=32, n_groups=8, t_max=1024, batch=4, d_c=1024), 1024, True),
+    (dict(n_heads=32, n_groups=8, t_max=1024, batch=4, d_c=1056), 1024, False),
+    (dict(n_heads=32, n_groups=8, t_max=4096, d_c=320), 768, True),
+    (dict(n_heads=32, n_groups=8, t_max=4096, d_c=352), 768, False),
+    (dict(n_heads=16, n_groups=4, t_max=256, d_v=64, d_c=256), 256, True),
+    (dict(n_heads=16, n_groups=4, t_max=256, d_v=64, d_c=288), 256, False),
+    (dict(n_heads=16, n_groups=2, t_max=256), 256, False),
 ])
 def test_prefill_routes(kw, n_new, inside):
     # the workspace is for the absorbed queries of the two-launch route
