@@ -51,23 +51,34 @@
 namespace {
 
 // ================================================================ append
-// Sixteen new rows per workgroup row, one group per wave: lane (n, qd) moves
-// pieces 4 k + qd of row n, so for rows at consecutive positions of one layout
-// tile (a prompt) a store covers 1 KB of contiguous memory and a row's reads
-// share cache lines; rows of different sequences (a decode batch) scatter as
-// they must.  The value pieces are requested before seq/pos are known (they
-// are indexed by the row alone): a single dependent round trip.  The
-// positional pairs, an fp64 rotation each, have workgroups of their own (the
-// last of gridDim.y), one pair per thread and pass.
+// Sixteen new rows per workgroup row; a wave moves 4 KP pieces of each for one
+// group: lane (n, qd) moves pieces 4 k + qd of row n, so for rows at
+// consecutive positions of one layout tile (a prompt) a store covers 1 KB of
+// contiguous memory and a row's reads share cache lines; rows of different
+// sequences (a decode batch) scatter as they must.  The pieces are requested
+// before seq/pos are known (they are indexed by the row alone): a single
+// dependent round trip.  The positional pairs, an fp64 rotation each, have
+// workgroups of their own (the last of gridDim.y), one pair per thread.
 // Bound by HBM for a prompt (8192 rows of 8 x 128 + 16 bf16 are read and
-// written, 34 MB), by latency for a batch.  One workgroup per row, half of its
-// threads idle, took 20.3 us for those 8192 rows; now 7 us.
+// written, 34 MB), by latency for a batch.  KP = 4 for a prompt (one workgroup
+// per row, half of its threads idle, took 20.3 us for those 8192 rows; now 7
+// us), 1 below one such workgroup per CU, so that a wide row is spread over
+// waves and nothing follows the first request (64 rows of G2 d 256 fp32 2.8 us,
+// 5.1 with the pieces past the first four of a lane in a loop and two pairs
+// per thread at d_r = 64; at the line, 512 rows of G32 d 128, 6.4 us with
+// KP = 4 and 7.0 with 1).
 constexpr int kAppendRows = 16;
 
-// workgroups over the groups (gridDim.y but for the positional keys')
-__host__ __device__ __forceinline__ int append_group_blocks(int G) {
-  const int n = (G + kWaves - 1) / kWaves;
-  return n < 4096 ? n : 4096;
+// waves over a row block's values: one per group and 4 KP pieces of its rows
+__host__ __device__ __forceinline__ int append_segs(int npc, int kp) { return (npc + 4 * kp - 1) / (4 * kp); }
+// workgroups over them (gridDim.y but for the positional keys')
+__host__ __device__ __forceinline__ int append_value_blocks(int G, int npc, int kp) {
+  const long long n = ((long long)G * append_segs(npc, kp) + kWaves - 1) / kWaves;
+  return (int)(n < 4096 ? n : 4096);
+}
+// and those over its positional pairs
+__host__ __device__ __forceinline__ int append_pair_blocks(int d_r) {
+  return (kAppendRows * (d_r / 2) + kThreads - 1) / kThreads;
 }
 
 // The streams holding row ps of sequence b: contiguous (b, g) streams, or,
@@ -95,53 +106,52 @@ __device__ __forceinline__ bool append_place(const AppendParams& p, int b, int p
   return true;
 }
 
-template <typename T>
+template <typename T, int KP>
 __global__ void __launch_bounds__(kThreads) append_kernel(AppendParams p) {
   constexpr int P = 16 / sizeof(T);
   const int r0 = blockIdx.x * kAppendRows;
   const int tid = threadIdx.x;
-  const int ngb = append_group_blocks(p.G);
+  const int npc = p.d_v / P;
+  const int nvb = append_value_blocks(p.G, npc, KP);
   AppendPlace at;
-  if ((int)blockIdx.y < ngb) {
+  if ((int)blockIdx.y < nvb) {
     const int lane = tid & 63, n = lane & 15, qd = lane >> 4;
     const int r = r0 + n;
     if (r >= p.n_rows) return;
-    const int npc = p.d_v / P;
-    for (int g = blockIdx.y * kWaves + (tid >> 6); g < p.G; g += ngb * kWaves) {
+    const int nseg = append_segs(npc, KP);
+    for (int64_t t = blockIdx.y * kWaves + (tid >> 6); t < (int64_t)p.G * nseg; t += nvb * kWaves) {
+      const int g = (int)(t / nseg), c0 = (int)(t % nseg) * 4 * KP + qd;
       const u32x4* src =
           reinterpret_cast<const u32x4*>(static_cast<const T*>(p.v_new) + ((int64_t)r * p.G + g) * p.d_v);
-      constexpr int kFirst = 4;                  // pieces requested ahead of seq/pos
-      u32x4 piece[kFirst];
+      u32x4 piece[KP];
 #pragma unroll
-      for (int k = 0; k < kFirst; ++k)
-        if (4 * k + qd < npc) piece[k] = src[4 * k + qd];
+      for (int k = 0; k < KP; ++k)
+        if (c0 + 4 * k < npc) piece[k] = src[c0 + 4 * k];
       if (!append_place(p, p.seq[r], p.pos[r], at)) return;
-      T* stream = static_cast<T*>(p.v_cache) + at.vstream0 + g * at.vstride + tiled_off<T>(at.row, qd * P, p.d_v);
+      T* stream = static_cast<T*>(p.v_cache) + at.vstream0 + g * at.vstride + tiled_off<T>(at.row, c0 * P, p.d_v);
       constexpr int kStep = 4 * kLayoutRows * P; // elements between pieces c and c + 4 of a row
 #pragma unroll
-      for (int k = 0; k < kFirst; ++k)
-        if (4 * k + qd < npc) *reinterpret_cast<u32x4*>(stream + k * kStep) = piece[k];
-      for (int k = kFirst; 4 * k + qd < npc; ++k)
-        *reinterpret_cast<u32x4*>(stream + (int64_t)k * kStep) = src[4 * k + qd];
+      for (int k = 0; k < KP; ++k)
+        if (c0 + 4 * k < npc) *reinterpret_cast<u32x4*>(stream + k * kStep) = piece[k];
     }
     return;
   }
   // positional keys: rotate pair i of row r at its position in fp64 (eq. krope)
   const int npair = p.d_r / 2;
-  for (int task = tid; task < kAppendRows * npair; task += kThreads) {
-    const int r = r0 + task / npair, i = task % npair;
-    if (r >= p.n_rows) break;
-    const T* kin = static_cast<const T*>(p.kr_new) + (int64_t)r * p.d_r + 2 * i;
-    const double k0 = load_elem<T>(kin, 0), k1 = load_elem<T>(kin, 1);
-    const int ps = p.pos[r];
-    if (!append_place(p, p.seq[r], ps, at)) continue;
-    double y0, y1;
-    rotate_pair(k0, k1, (double)ps * p.inv_freq[i], y0, y1);
-    T* kstream = static_cast<T*>(p.kr_cache) + at.kstream0;
-    const int64_t o = tiled_off<T>(at.row, 2 * i, p.d_r);  // the pair shares a piece
-    store_from_f64<T>(kstream, o, y0);
-    store_from_f64<T>(kstream, o + 1, y1);
-  }
+  const int task = ((int)blockIdx.y - nvb) * kThreads + tid;
+  if (task >= kAppendRows * npair) return;
+  const int r = r0 + task / npair, i = task % npair;
+  if (r >= p.n_rows) return;
+  const T* kin = static_cast<const T*>(p.kr_new) + (int64_t)r * p.d_r + 2 * i;
+  const double k0 = load_elem<T>(kin, 0), k1 = load_elem<T>(kin, 1);
+  const int ps = p.pos[r];
+  if (!append_place(p, p.seq[r], ps, at)) return;
+  double y0, y1;
+  rotate_pair(k0, k1, (double)ps * p.inv_freq[i], y0, y1);
+  T* kstream = static_cast<T*>(p.kr_cache) + at.kstream0;
+  const int64_t o = tiled_off<T>(at.row, 2 * i, p.d_r);  // the pair shares a piece
+  store_from_f64<T>(kstream, o, y0);
+  store_from_f64<T>(kstream, o + 1, y1);
 }
 
 // ================================================================ absorb
@@ -1689,12 +1699,14 @@ int append_impl(const gva_dims* dims, const gva_paging* paging, const int32_t* b
   p.n_pages = paging ? paging->n_pages : 0;
   fill_inv_freq(dims, p.inv_freq);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const dim3 grid((unsigned)((n_rows + (long long)kAppendRows - 1) / kAppendRows),
-                  (unsigned)(append_group_blocks(dims->n_groups) + (dims->d_r > 0 ? 1 : 0)));
-  if (dims->dtype == GVA_DTYPE_BF16)
-    hipLaunchKernelGGL(append_kernel<uint16_t>, grid, dim3(kThreads), 0, s, p);
-  else
-    hipLaunchKernelGGL(append_kernel<float>, grid, dim3(kThreads), 0, s, p);
+  const long long blocks = (n_rows + (long long)kAppendRows - 1) / kAppendRows;
+  const int npc = dims->d_v / (int)(16 / elem_size(dims));
+  const int kp = blocks * append_value_blocks(dims->n_groups, npc, 4) >= device_cu_count() ? 4 : 1;
+  const dim3 grid((unsigned)blocks,
+                  (unsigned)(append_value_blocks(dims->n_groups, npc, kp) + append_pair_blocks(dims->d_r)));
+  const auto fn = dims->dtype == GVA_DTYPE_BF16 ? (kp == 4 ? append_kernel<uint16_t, 4> : append_kernel<uint16_t, 1>)
+                                                : (kp == 4 ? append_kernel<float, 4> : append_kernel<float, 1>);
+  hipLaunchKernelGGL(fn, grid, dim3(kThreads), 0, s, p);
   return launch_status();
 }
 

@@ -384,6 +384,32 @@ def test_append_prompt_rows_edges(G, dv, dr, n, dtype):
     assert torch.equal(gva.untiled(kd.cpu()), k_ref) or dr == 0
 
 
+@pytest.mark.parametrize("G,dv,dr,n,dtype", [(9, 200, 16, 1003, "bf16"), (9, 20, 64, 1393, "f32")])
+def test_append_many_rows_edges(G, dv, dr, n, dtype):
+    # enough rows that a wave moves sixteen pieces of each (a workgroup of
+    # such waves per CU), rows of more pieces and of fewer, and of more
+    # positional pairs than one workgroup turns
+    waves = G * -(-dv * (2 if dtype == "bf16" else 4) // 256)
+    assert -(-n // 16) * -(-waves // 4) >= gva.device_cu_count(), "the shape must take the wide kernel"
+    T = 1408
+    w = gva_inputs.Workload("append", 1, T, 4 * G, G, dv, 64, dr, dtype=dtype)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(89)
+    v0, k0 = torch.randn(1, G, T, dv, generator=g).to(tdt), torch.randn(1, T, dr, generator=g).to(tdt)
+    v_new, k_new = torch.randn(n, G, dv, generator=g).to(tdt), torch.randn(n, dr, generator=g).to(tdt)
+    seq = torch.zeros(n, dtype=torch.int32)
+    pos = torch.randperm(T, generator=g)[:n].to(torch.int32)
+    seq[n // 3] = -1                           # skipped
+    v_ref, k_ref = v0.clone(), k0.clone()
+    oracle.append(v_ref, k_ref, v_new, k_new, seq, pos, w.rope_base)
+    vd, kd = gva.tiled(v0).cuda(), gva.tiled(k0).cuda()
+    note(f"append many rows G{G} d{dv}/{dr} n{n} {dtype}")
+    gva.gva_append_kv(dims_of(w), vd, kd, v_new.cuda(), k_new.cuda(), seq.cuda(), pos.cuda())
+    torch.cuda.synchronize()
+    assert torch.equal(gva.untiled(vd.cpu()), v_ref)
+    assert torch.equal(gva.untiled(kd.cpu()), k_ref)
+
+
 def test_combine_matches_oracle():
     B, H, S, dv = 3, 4, 9, 128
     g = torch.Generator().manual_seed(37)
