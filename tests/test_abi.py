@@ -137,7 +137,7 @@ def test_absorb_validation():
     assert lib.gva_absorb_query(None, A, A, A, A, A, None) == gva.GVA_ERR_INVALID_ARG
 
 
-def test_prefill_validation():
+def test_prefill_one_call_validation():
     # the one-call prompt: what the absorption and the attention refuse
     lib = gva.lib()
 
