@@ -263,8 +263,11 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 // 54.5, contiguous 42.9 and 44.8; B32 to 8192 rows, H16 G4 d 64, 8 splits,
 // 14.0 and 15.3; B64 to 8192 rows, H16 G2 d 128, 8 splits, 26.8 and 28.2).
 // With more splits the chunks are alike already and finding the order costs
-// more than it gives (B64 to 32K rows, 20 splits: 46.0 and 44.9), nor does it
-// pay with few sequences (B16 to 4096 rows, 8 splits: 18.7 and 18.1).
+// what it gives: over log-uniform lengths, longest first took 0.99 of the time
+// at 9 to 12 splits (10 batches of 32 to 64), 1.03 at 13 to 16 (21), 1.01 past
+// that; the planner's 16 splits of B64 to 32K rows 46.0 and 44.9 us.  Nor does
+// it pay with 16 to 31 sequences (0.98 to 1.02 over 238 batches; B16 to 4096
+// rows, 8 splits: 18.7 and 18.1).
 __device__ __forceinline__ bool longest_first(const DecodeArgs& p) { return p.B >= 32 && p.B <= 64 && p.S <= 8; }
 
 // Bounded chunks: slot i of the B * S (sequence, split) slots.  Slots are
