@@ -1364,11 +1364,10 @@ def test_prefill_sharp_scores(qscale):
     _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, f"prefill sharp scores x{qscale}")
 
 
-# Prompts large enough that the launch takes the columns-per-wave prefill
-# kernel (d_v = 128, d_r <= 32, at least 2 workgroups per CU -- 4 at
-# H/G = 8 -- of 4 x 32 columns): (B, H/G, G, d_r, N, prefix rows of the
-# other sequences, query scale).
-PREFILL_WAVE_CASES = [
+# Prompts of at least two workgroups of 128 columns per CU (the shared-tiles
+# kernel with one set of waves): (B, H/G, G, d_r, N, prefix rows of the other
+# sequences, query scale).
+PREFILL_LARGE_CASES = [
     (4, 4, 4, 16, 1024, 300, 1.0),
     (4, 8, 2, 16, 2048, 0, 1.0),
     (4, 1, 8, 0, 2048, 77, 1.0),
@@ -1378,50 +1377,50 @@ PREFILL_WAVE_CASES = [
 
 
 @pytest.mark.slow
-@pytest.mark.parametrize("B,hpg,G,dr,N,prefix,qscale", PREFILL_WAVE_CASES)
-def test_prefill_columns_per_wave_matches_oracle(B, hpg, G, dr, N, prefix, qscale):
+@pytest.mark.parametrize("B,hpg,G,dr,N,prefix,qscale", PREFILL_LARGE_CASES)
+def test_prefill_one_set_large_matches_oracle(B, hpg, G, dr, N, prefix, qscale):
     # every row of every prompt against the oracle; the first sequence's
     # prompt fills its cache from row 0, the others follow a cached prefix,
     # and rows past every length hold NaN
     n_cu = gva.device_cu_count()
     items = B * G * -(-N // (128 // hpg))
-    assert items >= (4 if hpg >= 8 else 2) * n_cu, "the shape must take the columns-per-wave kernel"
+    assert items >= 2 * n_cu, "the shape must take one set of waves"
     T = -(-(N + prefix) // 32) * 32              # the tiled layout's capacity granularity
-    w = gva_inputs.Workload("prefill_wave", B, T, hpg * G, G, 128, 128, dr, dtype="bf16")
+    w = gva_inputs.Workload("prefill_large", B, T, hpg * G, G, 128, 128, dr, dtype="bf16")
     lens = torch.tensor([N] + [N + prefix] * (B - 1), dtype=torch.int32)
     inp = gva_inputs.make_inputs(w, 47, lens=lens)
     for b, L in enumerate(lens.tolist()):
         inp["v"][b, :, L:] = float("nan")
         inp["kr"][b, L:] = float("nan")
     q = (gva_inputs.prefill_queries(w, 47, N).float() * qscale).to(torch.bfloat16)
-    note(f"prefill per wave B={B} hpg={hpg} G={G} dr={dr} N={N}: oracle")
+    note(f"prefill large B={B} hpg={hpg} G={G} dr={dr} N={N}: oracle")
     o_ref, lse_ref = oracle.prefill(q, inp["m"], inp["v"], inp["kr"], lens, rope_base=w.rope_base)
     dev = upload({k: inp[k] for k in ("m", "v", "kr", "lens")})
-    note(f"prefill per wave B={B} hpg={hpg} G={G} dr={dr} N={N}: GPU")
+    note(f"prefill large B={B} hpg={hpg} G={G} dr={dr} N={N}: GPU")
     o, lse = gva.prefill(dims_of(w), q.cuda(), dev["m"], dev["v"], dev["kr"], dev["lens"])
     torch.cuda.synchronize()
-    _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, f"prefill per wave hpg{hpg} G{G} dr{dr} N{N} x{qscale}")
+    _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, f"prefill large hpg{hpg} G{G} dr{dr} N{N} x{qscale}")
 
 
-# The matched-GQA prefill at sizes that take its columns-per-wave kernel
-# (16 columns per wave): (B, H/G, G, N, prefix rows of the other sequences).
-GQA_PREFILL_WAVE_CASES = [
-    (4, 4, 4, 512, 100),
-    (4, 8, 2, 1024, 0),
-    (4, 1, 8, 1024, 50),
+# The matched-GQA prefill on the shared-tiles kernel, d_v = 128: (B, H/G, G, N,
+# prefix rows of the other sequences, sets of waves the grid takes).
+GQA_PREFILL_LARGE_CASES = [
+    (4, 4, 4, 512, 100, 2),
+    (4, 8, 2, 1024, 0, 1),
+    (4, 1, 8, 1024, 50, 2),
 ]
 
 
 @pytest.mark.slow
-@pytest.mark.parametrize("B,hpg,G,N,prefix", GQA_PREFILL_WAVE_CASES)
-def test_gqa_prefill_columns_per_wave_matches_oracle(B, hpg, G, N, prefix):
+@pytest.mark.parametrize("B,hpg,G,N,prefix,sets", GQA_PREFILL_LARGE_CASES)
+def test_gqa_prefill_large_matches_oracle(B, hpg, G, N, prefix, sets):
     # sampled prompt rows (every seventh and the last) as GQA decode steps of
     # the oracle over the rows each sees
     n_cu = gva.device_cu_count()
-    items = B * G * -(-N // (64 // hpg))
-    assert items >= (4 if hpg >= 8 else 2) * n_cu, "the shape must take the columns-per-wave kernel"
+    items = B * G * -(-N // (128 // hpg))
+    assert (items >= 2 * n_cu) == (sets == 1) and 4 * items >= 3 * n_cu, "the shape must take this kernel"
     T = -(-(N + prefix) // 32) * 32
-    w = gva_inputs.Workload("gqa_prefill_wave", B, T, G * hpg, G, 128, 128, 0, dtype="bf16", gqa=True)
+    w = gva_inputs.Workload("gqa_prefill_large", B, T, G * hpg, G, 128, 128, 0, dtype="bf16", gqa=True)
     lens = torch.tensor([N] + [N + prefix] * (B - 1), dtype=torch.int32)
     inp = gva_inputs.make_inputs(w, 53, lens=lens)
     q = gva_inputs.prefill_queries(w, 53, N, gqa=True)
@@ -1429,7 +1428,7 @@ def test_gqa_prefill_columns_per_wave_matches_oracle(B, hpg, G, N, prefix):
     d = dims_of(w)
     o = torch.empty(B, N, w.n_heads, 128, dtype=torch.float32, device="cuda")
     lse = torch.empty(B, N, w.n_heads, dtype=torch.float32, device="cuda")
-    note(f"gqa prefill per wave B={B} hpg={hpg} G={G} N={N}")
+    note(f"gqa prefill large B={B} hpg={hpg} G={G} N={N}")
     gva.gva_gqa_prefill_attention(d, N, q.cuda(), dev["k_gqa"], dev["v"], dev["lens"], o, lse)
     torch.cuda.synchronize()
     o, lse = o.cpu(), lse.cpu()
@@ -1442,7 +1441,7 @@ def test_gqa_prefill_columns_per_wave_matches_oracle(B, hpg, G, N, prefix):
         o_ref[:, r] = oi
         lse_ref[:, r] = li
     idx = torch.tensor(rows)
-    _prefill_check(o[:, idx], lse[:, idx], o_ref, lse_ref, f"gqa prefill per wave hpg{hpg} G{G} N{N}")
+    _prefill_check(o[:, idx], lse[:, idx], o_ref, lse_ref, f"gqa prefill large hpg{hpg} G{G} N{N}")
 
 
 # Shapes on the edges of the kernel whose waves share key tiles through LDS
@@ -1616,6 +1615,120 @@ def test_gqa_prefill_matches_oracle(hpg, dv):
         o_ref[live, i] = oi[live]
         lse_ref[live, i] = li[live]
     _prefill_check(o, lse, o_ref, lse_ref, f"gqa prefill/hpg{hpg}/dv{dv}")
+
+
+def _gqa_prefill_check(w, N, lens, seed, label):
+    """The matched-GQA prefill of w's last N rows, every row as a GQA decode
+    step of the oracle over the rows it sees."""
+    inp = gva_inputs.make_inputs(w, seed, lens=lens)
+    for b, L in enumerate(lens.tolist()):
+        inp["v"][b, :, L:] = float("nan")
+        inp["k_gqa"][b, :, L:] = float("nan")
+    q = gva_inputs.prefill_queries(w, seed, N, gqa=True)
+    dev = upload({k: inp[k] for k in ("v", "k_gqa", "lens")})
+    o = torch.full((w.batch, N, w.n_heads, w.d_v), float("nan"), dtype=torch.float32, device="cuda")
+    lse = torch.full((w.batch, N, w.n_heads), float("nan"), dtype=torch.float32, device="cuda")
+    note(f"{label}: GPU")
+    gva.gva_gqa_prefill_attention(dims_of(w), N, q.cuda(), dev["k_gqa"], dev["v"], dev["lens"], o, lse)
+    torch.cuda.synchronize()
+    o_ref = torch.zeros(w.batch, N, w.n_heads, w.d_v, dtype=torch.float64)
+    lse_ref = torch.full((w.batch, N, w.n_heads), float("-inf"), dtype=torch.float64)
+    for i in range(N):
+        p = lens - N + i
+        live = p >= 0
+        if live.any():
+            oi, li = oracle.gqa_decode(q[:, i].contiguous(), inp["k_gqa"], inp["v"], (p + 1).clamp(min=0), d_k=w.d_v)
+            o_ref[live, i] = oi[live]
+            lse_ref[live, i] = li[live]
+    _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label)
+
+
+# The baseline on the shared-tiles kernel with one and two sets of waves: (B,
+# H/G, G, d_v, N, rows before the prompt, sets); an odd number of key tiles and
+# a last block of one position each, and prompts longer than their cache.
+@pytest.mark.parametrize("B,hpg,G,dv,N,prefix,sets", [
+    (8, 8, 4, 64, 97, 40, 2), (8, 2, 8, 128, 65, 3, 2), (16, 4, 8, 64, 97, -30, 1), (16, 8, 4, 128, 113, 20, 1)])
+def test_gqa_prefill_shared_tiles_matches_oracle(B, hpg, G, dv, N, prefix, sets):
+    n_cu = gva.device_cu_count()
+    items = B * G * -(-N // (128 // hpg))
+    assert (items >= 2 * n_cu) == (sets == 1) and 4 * items >= (2 if dv == 128 else 3) * n_cu
+    T = -(-(N + max(prefix, 0)) // 16) * 16
+    assert T <= 512, "half a workgroup per CU is enough for short caches"
+    w = gva_inputs.Workload("gqa_prefill_lds", B, T, G * hpg, G, dv, dv, 0, dtype="bf16", gqa=True)
+    lens = torch.tensor([N + prefix - 2 * (b % 5) for b in range(B)], dtype=torch.int32)
+    _gqa_prefill_check(w, N, lens, 61, f"gqa prefill lds B{B} hpg{hpg} G{G} d{dv} N{N}")
+
+
+# The tile-split kernel: few workgroups over a cache of more than 1024 rows.
+# (H/G, d_v, d_r, N): every instance (one positional chunk half used and
+# shared with its low part, one whole, two, none) at both widths, prompts of
+# one row, off and past a block.
+PREFILL_SPLIT_CASES = [(1, 64, 0, 100), (1, 128, 16, 33), (2, 64, 32, 33), (2, 128, 0, 100), (2, 128, 24, 1),
+                       (4, 64, 16, 33), (4, 128, 32, 33), (4, 64, 64, 100), (8, 128, 64, 33), (8, 64, 8, 1),
+                       (8, 64, 24, 100), (8, 128, 16, 100)]
+
+
+@pytest.mark.parametrize("hpg,dv,dr,N", PREFILL_SPLIT_CASES)
+def test_prefill_tile_split_matches_oracle(hpg, dv, dr, N):
+    # gva_prefill's two launches, the absorbed queries in the workspace (its
+    # size pins the route), NaN behind every length, one sequence shorter
+    # than the prompt, and sentinels around everything that is written
+    B, G, T, pad = 3, 2, 1040, 64
+    w = gva_inputs.Workload("prefill_split", B, T, hpg * G, G, dv, dv, dr, dtype="bf16")
+    lens = torch.tensor([T, 517, max(1, N - 12)], dtype=torch.int32)
+    inp = gva_inputs.make_inputs(w, 91, lens=lens)
+    for b, L in enumerate(lens.tolist()):
+        inp["v"][b, :, L:] = float("nan")
+        inp["kr"][b, L:] = float("nan")
+    q = gva_inputs.prefill_queries(w, 91, N)
+    label = f"prefill split hpg{hpg} d{dv}/{dr} N{N}"
+    o_ref, lse_ref = oracle.prefill(q, inp["m"], inp["v"], inp["kr"], lens, rope_base=w.rope_base)
+    dev = upload({k: inp[k] for k in ("m", "v", "kr", "lens")})
+    d = dims_of(w)
+    n = gva.gva_prefill_workspace_size(d, N)
+    rows = B * N * w.n_heads
+    assert n >= rows * (dv + dr) * 4, "the shape must take the two launches"
+    ws = torch.full((n + 512,), 0xA5, dtype=torch.uint8, device="cuda")
+    ob = torch.full((rows * dv + 2 * pad,), 7.0, dtype=torch.float32, device="cuda")
+    lb = torch.full((rows + 2 * pad,), 7.0, dtype=torch.float32, device="cuda")
+    o = ob[pad:-pad].view(B, N, w.n_heads, dv)
+    lse = lb[pad:-pad].view(B, N, w.n_heads)
+    note(f"{label}: GPU")
+    gva.gva_prefill(d, N, q.cuda(), dev["m"], dev["v"], dev["kr"], dev["lens"], o, lse, workspace=ws[256:256 + n])
+    torch.cuda.synchronize()
+    _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label)
+    for edge, value in ((ws[:256], 0xA5), (ws[256 + n:], 0xA5), (ob[:pad], 7.0), (ob[-pad:], 7.0), (lb[:pad], 7.0),
+                        (lb[-pad:], 7.0)):
+        assert bool((edge == value).all()), label
+
+
+@pytest.mark.parametrize("hpg,dv,N", [(1, 128, 33), (2, 64, 33), (4, 128, 50), (8, 128, 17), (8, 64, 50), (1, 64, 1)])
+def test_gqa_prefill_tile_split_matches_oracle(hpg, dv, N):
+    # few workgroups (and at d_v = 64 a cache of more than 1024 rows)
+    w = gva_inputs.Workload("gqa_prefill_split", 3, 1040, 2 * hpg, 2, dv, dv, 0, dtype="bf16", gqa=True)
+    lens = torch.tensor([1040, 517, max(1, N - 12)], dtype=torch.int32)
+    _gqa_prefill_check(w, N, lens, 97, f"gqa prefill split hpg{hpg} d{dv} N{N}")
+
+
+@pytest.mark.parametrize("B,hpg,G,dv,N,prefix", [(8, 8, 4, 64, 100, 200), (4, 4, 4, 128, 400, 90)])
+def test_prefill_two_sets_sharp_scores(B, hpg, G, dv, N, prefix):
+    # queries scaled by 6 with two sets of waves: each set moves its own
+    # running maximum between tiles, and the merge brings them together
+    n_cu = gva.device_cu_count()
+    items = B * G * -(-N // (128 // hpg))
+    assert 3 * n_cu <= 4 * items < 8 * n_cu, "the shape must take two sets"
+    T = -(-(N + prefix) // 16) * 16
+    w = gva_inputs.Workload("prefill_sharp", B, T, hpg * G, G, dv, dv, 16, dtype="bf16")
+    lens = torch.tensor([N + prefix - 7 * b for b in range(B)], dtype=torch.int32)
+    inp = gva_inputs.make_inputs(w, 101, lens=lens)
+    q = (gva_inputs.prefill_queries(w, 101, N).float() * 6.0).to(torch.bfloat16)
+    o_ref, lse_ref = oracle.prefill(q, inp["m"], inp["v"], inp["kr"], lens, rope_base=w.rope_base)
+    dev = upload({k: inp[k] for k in ("m", "v", "kr", "lens")})
+    label = f"prefill two sets sharp hpg{hpg} d{dv}"
+    note(f"{label}: GPU")
+    o, lse = gva.prefill(dims_of(w), q.cuda(), dev["m"], dev["v"], dev["kr"], dev["lens"])
+    torch.cuda.synchronize()
+    _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label)
 
 
 @pytest.mark.slow
