@@ -199,6 +199,16 @@ def test_f32_chunk_and_tile_edges(B, hpg, G, dv, dc, dr, T):
             assert torch.equal(gva.untiled(dev["kr"].cpu())[b, L - 1], k_ref[b, L - 1]) or dr == 0
 
 
+# More workgroups than CUs take four waves up to d_v = 128: each depth of the
+# tile pipeline and number of positional chunks there.
+@pytest.mark.parametrize("B,hpg,G,dv,dc,dr,T", [(90, 3, 3, 68, 40, 16, 32), (90, 1, 3, 128, 64, 32, 48),
+                                                (90, 2, 3, 100, 36, 64, 48), (90, 2, 3, 64, 40, 36, 32),
+                                                (90, 2, 3, 48, 24, 24, 32)])
+def test_f32_four_waves(B, hpg, G, dv, dc, dr, T):
+    assert B * G > gva.device_cu_count(), "the shape must take four waves"
+    test_f32_chunk_and_tile_edges(B, hpg, G, dv, dc, dr, T)
+
+
 @pytest.mark.parametrize("dr,hidden", [(12, float("-inf")), (16, torch.finfo(torch.float32).min)])
 def test_f32_rows_hidden_by_their_positional_keys(dr, hidden):
     # a whole 16-row tile (one wave's only one, or its first) with scores of
