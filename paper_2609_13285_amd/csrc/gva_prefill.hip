@@ -487,6 +487,13 @@ __device__ __forceinline__ void wait_copies() {   // until at most N of this wav
 // G4 d 64/16 1.01e-4, 1.10e-4, 7.3e-5; 512 tokens 1.17e-4, 1.32e-4, 6.2e-5).
 // It costs the 350M prompts 77.2 -> 80.9 us, 8192 tokens 752 -> 766.
 constexpr int kLowRows = 128;
+// The maximum's own weight is exact, so with sharp scores, whose outputs hang
+// on few weights, it moves sooner than the tile-split kernel's four do: at 8,
+// queries of 6 times the usual size came out up to 1.48 times as far off as
+// there, at 4 nowhere further (70 shapes at 1, 2.5 and 6 times; 0.50, 0.57 and
+// 0.62 of its error on average; at 10 times 7 of 70, up to 1.13).  8192 tokens 812 and 819 us, four 350M prompts
+// 77.4 and 78.1; at 2, 836 and 79.5.
+constexpr float kLdsLazyMax = 4.f;
 
 // The workgroup's barrier, which alone orders no memory access for the
 // compiler: accesses stay on their side of it.
@@ -843,8 +850,8 @@ __global__ void __launch_bounds__(256 * KS, 2) prefill_lds_kernel(PrefillParams 
       mt = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     }
     // The maximum is the first tile's with a row that counts, and moves when
-    // a column's tile maximum exceeds it by more than kLazyMax (log2 units).
-    if (FIRST || __ballot(mt > m_run + kLazyMax) != 0) {
+    // a column's tile maximum exceeds it by more than kLdsLazyMax (log2 units).
+    if (FIRST || __ballot(mt > m_run + kLdsLazyMax) != 0) {
       const float m_new = fmaxf(mt, m_run);
       if constexpr (!FIRST) {
         const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);

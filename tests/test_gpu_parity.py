@@ -1720,10 +1720,12 @@ def test_gqa_prefill_tile_split_matches_oracle(hpg, dv, N):
     _gqa_prefill_check(w, N, lens, 97, f"gqa prefill split hpg{hpg} d{dv} N{N}")
 
 
-@pytest.mark.parametrize("B,hpg,G,dv,N,prefix", [(8, 8, 4, 64, 100, 200), (4, 4, 4, 128, 400, 90)])
-def test_prefill_two_sets_sharp_scores(B, hpg, G, dv, N, prefix):
+@pytest.mark.parametrize("B,hpg,G,dv,N,prefix,rel", [(8, 8, 4, 64, 100, 200, 5.45e-5), (4, 4, 4, 128, 400, 90, 6.45e-5)])
+def test_prefill_two_sets_sharp_scores(B, hpg, G, dv, N, prefix, rel):
     # queries scaled by 6 with two sets of waves: each set moves its own
-    # running maximum between tiles, and the merge brings them together
+    # running maximum between tiles, and the merge brings them together.  rel:
+    # the relative error of the tile-split kernel on the same inputs, which
+    # has four maxima per column (an exact weight each) where this has two.
     n_cu = gva.device_cu_count()
     items = B * G * -(-N // (128 // hpg))
     assert 3 * n_cu <= 4 * items < 8 * n_cu, "the shape must take two sets"
@@ -1739,6 +1741,8 @@ def test_prefill_two_sets_sharp_scores(B, hpg, G, dv, N, prefix):
     o, lse = gva.prefill(dims_of(w), q.cuda(), dev["m"], dev["v"], dev["kr"], dev["lens"])
     torch.cuda.synchronize()
     _prefill_check(o.cpu(), lse.cpu(), o_ref, lse_ref, label)
+    err = float((o.cpu().double() - o_ref).norm() / o_ref.norm())
+    assert err <= rel, (label, err)
 
 
 @pytest.mark.slow
