@@ -62,11 +62,12 @@ namespace {
 // Bound by HBM for a prompt (8192 rows of 8 x 128 + 16 bf16 are read and
 // written, 34 MB), by latency for a batch.  KP = 4 for a prompt (one workgroup
 // per row, half of its threads idle, took 20.3 us for those 8192 rows; now 7
-// us), 1 below one such workgroup per CU, so that a wide row is spread over
-// waves and nothing follows the first request (64 rows of G2 d 256 fp32 2.8 us,
-// 5.1 with the pieces past the first four of a lane in a loop and two pairs
-// per thread at d_r = 64; at the line, 512 rows of G32 d 128, 6.4 us with
-// KP = 4 and 7.0 with 1).
+// us), 1 below 3/8 of such a workgroup per CU, so that a wide row is spread
+// over waves and nothing follows the first request (64 rows of G2 d 256 fp32
+// 2.8 us, 5.1 with the pieces past the first four of a lane in a loop and two
+// pairs per thread at d_r = 64).  At the line, KP = 4 and 1: 700 prompt rows of
+// G8 d 128, 88 workgroups, 3.3 and 3.3 us; 1000, 126, 3.4 and 3.6; 512 scattered
+// ones, 64, 4.0 and 3.6.
 constexpr int kAppendRows = 16;
 
 // waves over a row block's values: one per group and 4 KP pieces of its rows
@@ -1701,7 +1702,7 @@ int append_impl(const gva_dims* dims, const gva_paging* paging, const int32_t* b
   hipStream_t s = static_cast<hipStream_t>(stream);
   const long long blocks = (n_rows + (long long)kAppendRows - 1) / kAppendRows;
   const int npc = dims->d_v / (int)(16 / elem_size(dims));
-  const int kp = blocks * append_value_blocks(dims->n_groups, npc, 4) >= device_cu_count() ? 4 : 1;
+  const int kp = 8 * blocks * append_value_blocks(dims->n_groups, npc, 4) >= 3LL * device_cu_count() ? 4 : 1;
   const dim3 grid((unsigned)blocks,
                   (unsigned)(append_value_blocks(dims->n_groups, npc, kp) + append_pair_blocks(dims->d_r)));
   const auto fn = dims->dtype == GVA_DTYPE_BF16 ? (kp == 4 ? append_kernel<uint16_t, 4> : append_kernel<uint16_t, 1>)
