@@ -341,9 +341,10 @@ int gva_prefill_attention(const gva_dims* dims, int32_t n_new, const float* q_ab
  * gva_prefill_workspace_size, gva_prefill -- gva_prefill_absorb and
  * gva_prefill_attention in one call: o and lse of a prompt's rows from the
  * raw queries q [B][n_new][H][d_c+d_r] and the maps m.  Where the grid is
- * large enough the absorption runs inside the attention launch and the
- * absorbed queries never reach memory; otherwise (short prompts) the call
- * makes the two launches, with the absorbed queries in `workspace`, a
+ * large enough, or the cache short, and the maps not too wide, the absorption
+ * runs inside the attention launch and the absorbed queries never reach
+ * memory; otherwise the call makes the two launches, with the absorbed
+ * queries in `workspace`, a
  * caller-owned device buffer of at least the bytes
  * gva_prefill_workspace_size reports for the same dims and n_new on the
  * current device, 256-byte aligned (0 bytes: workspace may be NULL).  Its

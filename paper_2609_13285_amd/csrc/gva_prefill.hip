@@ -435,17 +435,17 @@ constexpr int kPrefillCols = 128;             // (position, head) columns per wo
 //    baseline below.)
 // One barrier per tile.
 //
-// What bounds it: at d_v = 128 the matrix cores' power.  They are busy 63% of
-// the cycles, at which the clock settles at 1.9 GHz (a large bf16 library
-// product: 70% at 2.0 GHz; the kernel this replaced, every wave reading whole
-// tiles into registers and transposing in 16-wide products: 49% at 2.3 GHz).
-// At d_v = 64 the softmax, twice as much per product, and each workgroup's
-// start.  Measured, append and prompt from the raw queries against the
-// separate absorption and the former kernels: H32 G8 d 128/16, 8192 tokens
-// 899 -> 759 us; H16 G4 d 64/16, four 2048-token prompts 141 -> 76.5 us; the
-// matched-GQA baseline at H32 G8 d 128, 4096 tokens 310 -> 197 us.  With 168
-// registers for three waves per SIMD at d_v = 64, 8192 tokens took 258 us
-// against 240 (spills).
+// What bounds it: at d_v = 128 the matrix cores' power.  They are busy 70% of
+// the cycles, at which the clock settles at 1.7 GHz (a large bf16 library
+// product: 69% at 1.9 GHz).  At d_v = 64, busy 44% at 2.0 GHz, the softmax,
+// twice as much per product, and each workgroup's start.  Measured, append and
+// prompt from the raw queries against the separate absorption and the kernels
+// before: H32 G8 d 128/16, 8192 tokens 900 -> 778 us; H16 G4 d 64/16, four
+// 2048-token prompts 141 -> 76.7 us; the matched-GQA baseline at H32 G8 d 128,
+// 4096 tokens 311 -> 193 us.  Registers: d_v = 128 takes all of two waves per
+// SIMD, and its instances of two and four positional chunks keep 8 or 9 and 26
+// to 28 of them in scratch around the key loop (none inside it); d_v = 64 with
+// d_r <= 16 takes 161 to 163, so three workgroups of one set fit a CU.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
