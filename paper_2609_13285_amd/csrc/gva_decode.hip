@@ -1181,18 +1181,16 @@ __global__ void __launch_bounds__(64 * NW, NW == kWaves && NC <= 8 ? 2 : 1)
 
   auto compute_tile = [&](TileF& t, int row0, int row_end) __attribute__((always_inline)) {
     const bool tail = row0 + kF32TileRows > row_end;
-    if (tail) {                                // rows past the end may hold anything
+    // rows past the end may hold anything, and an infinity read again past the
+    // row's width would meet the query's zero.  (One branch for both: with a
+    // second one the d_v = 256 instance took 240 us where it takes 221, B100
+    // T1024 H32 G4.)
+    if (tail || ragged) {
       const bool dead = row0 + n >= row_end;
 #pragma unroll
-      for (int c = 0; c < NC; ++c) t.v[c] = dead ? zero4 : t.v[c];
+      for (int c = 0; c < NC; ++c) t.v[c] = dead || 16 * c + 4 * qd >= DV ? zero4 : t.v[c];
 #pragma unroll
-      for (int c = 0; c < NRC; ++c) t.k[c] = dead ? zero4 : t.k[c];
-    }
-    if (ragged) {                              // an infinity read again there would meet the query's zero
-#pragma unroll
-      for (int c = 0; c < NC; ++c) t.v[c] = 16 * c + 4 * qd < DV ? t.v[c] : zero4;
-#pragma unroll
-      for (int c = 0; c < NRC; ++c) t.k[c] = 16 * c + 4 * qd < DR ? t.k[c] : zero4;
+      for (int c = 0; c < NRC; ++c) t.k[c] = dead || 16 * c + 4 * qd >= DR ? zero4 : t.k[c];
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4*>(tr + n * PITCH + 16 * c + 4 * qd) = t.v[c];
