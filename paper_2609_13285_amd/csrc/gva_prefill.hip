@@ -1040,7 +1040,10 @@ PrefillFn pick_prefill(int hpg, int dv, int d_r, bool gqa) {
 //    and 28).  At d_v = 128 up to 128 rows, or 256 with the absorption's
 //    launch to save (H32 G8, 256 tokens: 19 and 24), to 512 the larger the
 //    prompt (512 tokens, 128 workgroups: 25 and 33; H4 G2, 16 workgroups: 24
-//    and 22), and never for the baseline (128 tokens: 11 us, 9 tile-split).
+//    and 22; H24 G6, 720 tokens, 138 workgroups, which are two rounds of
+//    tile-split ones: 29 and 44), to 1024 at 128 workgroups if its blocks are
+//    long on average too (512 after 512: 38 and 40; H16 G16, 1024 tokens: 36
+//    and 31), and never for the baseline (128 tokens: 11 us, 9 tile-split).
 enum class Prompt { kAttention, kWhole, kGqa };   // absorbed queries, raw ones (gva_prefill), the baseline
 
 struct PrefillPlan {
@@ -1088,7 +1091,9 @@ PrefillPlan prefill_plan(const gva_dims* d, int n_new, Prompt kind) {
   }
   if (!cols32 || kind == Prompt::kGqa) return {0, false};
   const int passes = hpg == 8 ? 2 : 1;         // of a wave's absorption
-  if (whole && T <= 512 && passes * T * n_cu <= 2048 * items && passes * d->d_c <= 256) return {1, true};
+  const bool larger = T <= 512 || 2 * items > n_cu || 4 * mean2 >= 3 * (double)n_cu;
+  if (whole && T <= 1024 && passes * T * n_cu <= (larger ? 2048 : 1664) * items && passes * d->d_c <= 256)
+    return {1, true};
   if (T <= (whole ? 256 : 128)) return {1, whole && absorb_inside(d, 1, false)};
   return {0, false};
 }

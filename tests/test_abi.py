@@ -164,7 +164,11 @@ def test_prefill_one_call_validation():
 @pytest.mark.parametrize("kw,n_new,inside", [
     # d_v = 128, few workgroups: by the cache's length against the prompt's size
     (dict(n_heads=32, n_groups=8, t_max=1024), 64, False),
-    (dict(n_heads=32, n_groups=8, t_max=1024), 512, False),
+    (dict(n_heads=32, n_groups=8, t_max=1024), 512, True),
+    (dict(n_heads=32, n_groups=8, t_max=1024), 480, False),
+    (dict(n_heads=16, n_groups=16, t_max=1024), 1024, False),
+    (dict(n_heads=24, n_groups=6, t_max=720), 720, True),
+    (dict(n_heads=32, n_groups=8, t_max=800), 512, True),
     (dict(n_heads=32, n_groups=8, t_max=512), 512, True),
     (dict(n_heads=4, n_groups=2, t_max=512), 512, False),
     (dict(n_heads=32, n_groups=8, t_max=256), 256, True),
